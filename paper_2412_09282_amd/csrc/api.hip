@@ -566,8 +566,8 @@ crvq_status crvq_gram(const void* X, int x_dtype, int64_t n_rows, int64_t n_cols
   if (ld < n_cols || ldh < n_cols) return fail(CRVQ_ERR_INVALID, "%s: ld and ldh must be >= n_cols", fn);
   if (n_cols == 0) return CRVQ_OK;
   if (!H || (n_rows > 0 && !X)) return fail(CRVQ_ERR_INVALID, "%s: X and H must not be NULL", fn);
-  return hip_status(launch_gemm_f64(n_cols, n_cols, n_rows, X, x_dtype == CRVQ_F32 ? ET_F32 : ET_F64, true, ld, X,
-                                    x_dtype == CRVQ_F32 ? ET_F32 : ET_F64, ld, H, ldh, static_cast<hipStream_t>(stream)),
+  return hip_status(launch_gram_f64(n_cols, n_rows, X, x_dtype == CRVQ_F32 ? ET_F32 : ET_F64, ld, H, ldh,
+                                    static_cast<hipStream_t>(stream)),
                     fn);
 }
 
@@ -604,7 +604,7 @@ crvq_status crvq_hessian_product(int64_t M, int64_t N, int64_t n_out, const doub
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (M == 0) return loss_total ? hip_status(launch_sum_f64(0, nullptr, loss_total, st), fn) : CRVQ_OK;
   if (!R || !H || !G) return fail(CRVQ_ERR_INVALID, "%s: R, H and G must not be NULL", fn);
-  crvq_status s = hip_status(launch_gemm_f64(M, n_out, N, R, ET_F64, false, ldr, H, ET_F64, ldh, G, ldg, st), fn);
+  crvq_status s = hip_status(launch_gemm_f64(M, n_out, N, R, ldr, H, ldh, G, ldg, false, st), fn);
   if (s || !row_loss) return s;
   if ((s = hip_status(launch_row_dot(M, N, R, ldr, G, ldg, row_loss, st), fn)) || !loss_total) return s;
   return hip_status(launch_sum_f64(M, row_loss, loss_total, st), fn);

@@ -203,9 +203,16 @@ hipError_t launch_gemv(int64_t M, int64_t N, int64_t n_crit, const uint8_t* q_ba
 hipError_t launch_pack_codes_u8(const int32_t* codes, int64_t n, uint8_t* out, hipStream_t stream);
 
 // ---- loss-driven refinement (k_refine.hip) ---------------------------------------------------------
-hipError_t launch_gemm_f64(int64_t M, int64_t Nc, int64_t Kd, const void* A, int a_type, bool trans_a, int64_t lda,
-                           const void* B, int b_type, int64_t ldb, double* C, int64_t ldc, hipStream_t stream,
-                           bool sub = false);
+// fp64 products on the matrix cores (k_gemm.hip): H = X^T X (N x N, X rows x N of ET_F32 or ET_F64);
+// C = A B, or C -= A B when sub; the same split over k into gemm_split_parts(M, Nc, Kd) parts kept in
+// ws (that many M x Nc arrays) when the output alone is too small to fill the device.
+hipError_t launch_gram_f64(int64_t N, int64_t rows, const void* X, int type, int64_t ld, double* H, int64_t ldh,
+                           hipStream_t stream);
+hipError_t launch_gemm_f64(int64_t M, int64_t Nc, int64_t Kd, const double* A, int64_t lda, const double* B,
+                           int64_t ldb, double* C, int64_t ldc, bool sub, hipStream_t stream);
+int64_t gemm_split_parts(int64_t M, int64_t Nc, int64_t Kd);
+hipError_t launch_gemm_f64_split(int64_t M, int64_t Nc, int64_t Kd, const double* A, int64_t lda, const double* B,
+                                 int64_t ldb, double* C, int64_t ldc, double* ws, hipStream_t stream);
 hipError_t launch_row_dot(int64_t M, int64_t n, const double* A, int64_t lda, const double* B, int64_t ldb,
                           double* out, hipStream_t stream);
 hipError_t launch_sum_f64(int64_t n, const double* x, double* out, hipStream_t stream);

@@ -4,8 +4,6 @@
 //   QuantLoss = ||W X^T - W_hat X^T||^2 = sum_r R_r H R_r^T,  dQuantLoss / dW_hat = -2 R H.
 //
 // Kernels:
-//  * gemm_f64_kernel: C = op(A) B in fp64 (H = X^T X from fp32 activations, G = R H), a 128 x 128
-//    tile per workgroup, 8 x 8 outputs per thread, operands staged through LDS as fp64.
 //  * row_dot_kernel: the per-row loss sum_j R_rj G_rj in a fixed order.
 //  * code_sum_wave_partial (K <= 256, d <= 8) or code_sum_partial, then code_sum_final: per-code sums
 //    of fp64 vectors (the codebook gradient) in a fixed order -- per-wave LDS tables filled by ballot
@@ -20,186 +18,6 @@
 
 namespace crvq {
 namespace {
-
-constexpr int kGBM = 128, kGBN = 128, kGBK = 8;
-#ifndef CRVQ_GEMM_MFMA
-#define CRVQ_GEMM_MFMA 1  // fp64 products without transpose on the matrix cores
-#endif
-
-template <typename T>
-__device__ __forceinline__ double to_f64(T x) {
-  return static_cast<double>(x);
-}
-
-// C[i][j] = sum_k opA(i, k) B(k, j) (or C[i][j] - that sum when SUB) for i < M, j < Nc, k < Kd, where
-// opA(i, k) = A[i * lda + k], or A[k * lda + i] when TRANS_A, and B(k, j) = B[k * ldb + j].  Products are formed in fp64 (exact for
-// fp32 operands) and accumulated with fused multiply-adds in k order.
-template <typename TA, typename TB, bool TRANS_A, bool SUB>
-__global__ __launch_bounds__(256) void gemm_f64_kernel(int64_t M, int64_t Nc, int64_t Kd, const TA* __restrict__ A,
-                                                       int64_t lda, const TB* __restrict__ B, int64_t ldb,
-                                                       double* __restrict__ C, int64_t ldc, int64_t kchunk,
-                                                       int64_t c_part) {
-  __shared__ double As[kGBK][kGBM];
-  __shared__ double Bs[kGBK][kGBN];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int64_t i0 = static_cast<int64_t>(blockIdx.y) * kGBM, j0 = static_cast<int64_t>(blockIdx.x) * kGBN;
-  // split over k: part blockIdx.z takes k in [kb, ke) and writes its own slice of C
-  const int64_t kb = static_cast<int64_t>(blockIdx.z) * kchunk;
-  const int64_t ke = kb + kchunk < Kd ? kb + kchunk : Kd;
-  C += static_cast<int64_t>(blockIdx.z) * c_part;
-  double acc[8][8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.0;
-  for (int64_t k0 = kb; k0 < ke; k0 += kGBK) {
-#pragma unroll
-    for (int s = 0; s < kGBM * kGBK / 256; ++s) {
-      const int e = tid + 256 * s;
-      int ii, kk;
-      if (TRANS_A) {  // consecutive threads read consecutive i (contiguous in memory)
-        ii = e % kGBM;
-        kk = e / kGBM;
-      } else {        // consecutive threads read consecutive k of one row
-        kk = e % kGBK;
-        ii = e / kGBK;
-      }
-      const int64_t gi = i0 + ii, gk = k0 + kk;
-      double v = 0.0;
-      if (gi < M && gk < ke) v = to_f64(TRANS_A ? A[gk * lda + gi] : A[gi * lda + gk]);
-      As[kk][ii] = v;
-    }
-#pragma unroll
-    for (int s = 0; s < kGBN * kGBK / 256; ++s) {
-      const int e = tid + 256 * s;
-      const int jj = e % kGBN, kk = e / kGBN;
-      const int64_t gj = j0 + jj, gk = k0 + kk;
-      Bs[kk][jj] = (gj < Nc && gk < ke) ? to_f64(B[gk * ldb + gj]) : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < kGBK; ++kk) {
-      double a[8], b[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) b[j] = Bs[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int64_t gi = i0 + ty + 16 * i;
-    if (gi >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int64_t gj = j0 + tx + 16 * j;
-      if (gj < Nc) C[gi * ldc + gj] = SUB ? C[gi * ldc + gj] - acc[i][j] : acc[i][j];
-    }
-  }
-}
-
-// The same product for fp64 A (row-major, not transposed) and B on the matrix cores: a 32 MW x 32 MW
-// tile of C per workgroup, 16 MW x 16 MW per wave as MW x MW v_mfma_f64_16x16x4f64 tiles (MW = 4 for
-// the long products, 2 for the short-k updates of the code search, which need more workgroups in
-// flight to hide their loads), k staged through
-// LDS 16 at a time (k-major, so the 16 lanes of an operand group read consecutive doubles).  Lane l
-// of an MFMA supplies A[i0 + l % 16][k + l / 16] and B[k + l / 16][j0 + l % 16] and holds
-// C[i0 + l / 16 + 4 r][j0 + l % 16], r < 4.  Each element is an fp64 dot product over its k range
-// (the matrix core's accumulation within a group of 4, then k order).
-constexpr int kMT = 128;  // C tile per workgroup and dimension of the long products (MW = 4)
-constexpr int kMK = 16;   // k per LDS stage
-typedef double d4v __attribute__((ext_vector_type(4)));
-template <bool SUB, int kMW, typename TA = double, typename TB = double, bool TRANS_A = false>
-__global__ __launch_bounds__(256) void gemm_f64_mfma_kernel(int64_t M, int64_t Nc, int64_t Kd, const TA* __restrict__ A,
-                                                            int64_t lda, const TB* __restrict__ B, int64_t ldb,
-                                                            double* __restrict__ C, int64_t ldc, int64_t kchunk,
-                                                            int64_t c_part) {
-  constexpr int kMT = 2 * 16 * kMW;  // C tile per workgroup and dimension (2 x 2 waves)
-  __shared__ double As[kMK][kMT + 2];
-  __shared__ double Bs[kMK][kMT + 2];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wi = (wave >> 1) * 16 * kMW, wj = (wave & 1) * 16 * kMW;
-  const int li = lane & 15, lk = lane >> 4;
-  const int64_t i0 = static_cast<int64_t>(blockIdx.y) * kMT, j0 = static_cast<int64_t>(blockIdx.x) * kMT;
-  const int64_t kb = static_cast<int64_t>(blockIdx.z) * kchunk;
-  const int64_t ke = kb + kchunk < Kd ? kb + kchunk : Kd;
-  C += static_cast<int64_t>(blockIdx.z) * c_part;
-  d4v acc[kMW][kMW];
-#pragma unroll
-  for (int a = 0; a < kMW; ++a)
-#pragma unroll
-    for (int b = 0; b < kMW; ++b) acc[a][b] = d4v{0.0, 0.0, 0.0, 0.0};
-  // stage k0's operands are read into registers one stage ahead, so their loads overlap the MFMAs
-  constexpr int kL = kMT * kMK / 256;
-  double pa[kL], pb[kL];
-  auto fetch = [&](int64_t k0) {
-#pragma unroll
-    for (int s = 0; s < kL; ++s) {
-      const int e = tid + 256 * s;
-      // consecutive threads: consecutive k of one row of A, or consecutive i of one row of A^T
-      const int kk = TRANS_A ? e / kMT : e % kMK, ii = TRANS_A ? e % kMT : e / kMK;
-      const int64_t gi = i0 + ii, gk = k0 + kk;
-      pa[s] = (gi < M && gk < ke) ? to_f64(TRANS_A ? A[gk * lda + gi] : A[gi * lda + gk]) : 0.0;
-      const int jj = e % kMT, kb2 = e / kMT;  // consecutive threads: consecutive j of one row of B
-      const int64_t gj = j0 + jj, gk2 = k0 + kb2;
-      pb[s] = (gj < Nc && gk2 < ke) ? to_f64(B[gk2 * ldb + gj]) : 0.0;
-    }
-  };
-  if (kb < ke) fetch(kb);
-  for (int64_t k0 = kb; k0 < ke; k0 += kMK) {
-#pragma unroll
-    for (int s = 0; s < kL; ++s) {
-      const int e = tid + 256 * s;
-      if (TRANS_A)
-        As[e / kMT][e % kMT] = pa[s];
-      else
-        As[e % kMK][e / kMK] = pa[s];
-      Bs[e / kMT][e % kMT] = pb[s];
-    }
-    __syncthreads();
-    if (k0 + kMK < ke) fetch(k0 + kMK);
-#pragma unroll
-    for (int ks = 0; ks < kMK; ks += 4) {
-      double a[kMW], b[kMW];
-#pragma unroll
-      for (int t = 0; t < kMW; ++t) {
-        a[t] = As[ks + lk][wi + 16 * t + li];
-        b[t] = Bs[ks + lk][wj + 16 * t + li];
-      }
-#pragma unroll
-      for (int ta = 0; ta < kMW; ++ta)
-#pragma unroll
-        for (int tb = 0; tb < kMW; ++tb)
-          acc[ta][tb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int ta = 0; ta < kMW; ++ta)
-#pragma unroll
-    for (int tb = 0; tb < kMW; ++tb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t gi = i0 + wi + 16 * ta + lk + 4 * r, gj = j0 + wj + 16 * tb + li;
-        if (gi < M && gj < Nc) C[gi * ldc + gj] = SUB ? C[gi * ldc + gj] - acc[ta][tb][r] : acc[ta][tb][r];
-      }
-}
-
-// C[i][j] = sum over parts p = 0 .. P - 1 in order of part[p][i][j] (the split-k partial products).
-__global__ __launch_bounds__(256) void sum_parts_kernel(int64_t M, int64_t Nc, int P, const double* __restrict__ part,
-                                                        double* __restrict__ C, int64_t ldc) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= M * Nc) return;
-  double acc = part[e];
-  for (int p = 1; p < P; ++p) acc = acc + part[static_cast<int64_t>(p) * M * Nc + e];
-  const int64_t i = e / Nc, j = e - i * Nc;
-  C[i * ldc + j] = acc;
-}
 
 // out[r] = sum_{j < n} A[r * lda + j] * B[r * ldb + j]: strided per-thread sums, then a fixed tree.
 __global__ __launch_bounds__(256) void row_dot_kernel(int64_t n, const double* __restrict__ A, int64_t lda,
@@ -775,73 +593,6 @@ __global__ __launch_bounds__(256) void refine_apply_kernel(int64_t M, int d, int
 }  // namespace
 
 // ---- launchers -----------------------------------------------------------------------------------
-hipError_t launch_gemm_f64(int64_t M, int64_t Nc, int64_t Kd, const void* A, int a_type, bool trans_a, int64_t lda,
-                           const void* B, int b_type, int64_t ldb, double* C, int64_t ldc, hipStream_t stream,
-                           bool sub) {
-  if (M <= 0 || Nc <= 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>(cdiv(Nc, kGBN)), static_cast<unsigned>(cdiv(M, kGBM)));
-#define CRVQ_GEMM(TA, TB, TR, SB)                                                                          \
-  hipLaunchKernelGGL((gemm_f64_kernel<TA, TB, TR, SB>), grid, dim3(256), 0, stream, M, Nc, Kd,             \
-                     static_cast<const TA*>(A), lda, static_cast<const TB*>(B), ldb, C, ldc, Kd, int64_t{0})
-  if (a_type == ET_F32 && b_type == ET_F32 && !sub && trans_a && CRVQ_GEMM_MFMA) {
-    // the Gram matrix X^T X of fp32 activations, widened exactly on load
-    const dim3 gm(static_cast<unsigned>(cdiv(Nc, kMT)), static_cast<unsigned>(cdiv(M, kMT)));
-    hipLaunchKernelGGL((gemm_f64_mfma_kernel<false, 4, float, float, true>), gm, dim3(256), 0, stream, M, Nc, Kd,
-                       static_cast<const float*>(A), lda, static_cast<const float*>(B), ldb, C, ldc, Kd, int64_t{0});
-  } else if (a_type == ET_F32 && b_type == ET_F32 && !sub) {
-    if (trans_a) CRVQ_GEMM(float, float, true, false); else CRVQ_GEMM(float, float, false, false);
-  } else if (a_type == ET_F64 && b_type == ET_F64 && !trans_a && CRVQ_GEMM_MFMA) {
-    const dim3 gm(static_cast<unsigned>(cdiv(Nc, kMT)), static_cast<unsigned>(cdiv(M, kMT)));
-    const dim3 gs(static_cast<unsigned>(cdiv(Nc, kMT / 2)), static_cast<unsigned>(cdiv(M, kMT / 2)));
-    if (sub)
-      hipLaunchKernelGGL((gemm_f64_mfma_kernel<true, 2>), gs, dim3(256), 0, stream, M, Nc, Kd,
-                         static_cast<const double*>(A), lda, static_cast<const double*>(B), ldb, C, ldc, Kd, int64_t{0});
-    else
-      hipLaunchKernelGGL((gemm_f64_mfma_kernel<false, 4>), gm, dim3(256), 0, stream, M, Nc, Kd,
-                         static_cast<const double*>(A), lda, static_cast<const double*>(B), ldb, C, ldc, Kd, int64_t{0});
-  } else if (a_type == ET_F64 && b_type == ET_F64 && !(trans_a && sub)) {
-    if (trans_a) CRVQ_GEMM(double, double, true, false);
-    else if (sub) CRVQ_GEMM(double, double, false, true);
-    else CRVQ_GEMM(double, double, false, false);
-  } else {
-    return hipErrorInvalidValue;
-  }
-#undef CRVQ_GEMM
-  return hipGetLastError();
-}
-
-// C = A B (fp64, row-major, no transpose) split over k into P parts of at least 512 when the output
-// grid alone is too small to fill the device; part products go to ws (P x M x Nc doubles) and are
-// summed in part order, so the result does not depend on scheduling.
-int64_t gemm_split_parts(int64_t M, int64_t Nc, int64_t Kd) {
-  const int64_t tiles = CRVQ_GEMM_MFMA ? cdiv(Nc, kMT) * cdiv(M, kMT) : cdiv(Nc, kGBN) * cdiv(M, kGBM);
-  int64_t P = tiles >= 256 ? 1 : cdiv(512, tiles);
-  const int64_t maxp = Kd / 512 > 1 ? Kd / 512 : 1;
-  return P < maxp ? P : maxp;
-}
-
-hipError_t launch_gemm_f64_split(int64_t M, int64_t Nc, int64_t Kd, const double* A, int64_t lda, const double* B,
-                                 int64_t ldb, double* C, int64_t ldc, double* ws, hipStream_t stream) {
-  if (M <= 0 || Nc <= 0) return hipSuccess;
-  const int64_t P = gemm_split_parts(M, Nc, Kd);
-  if (P <= 1) return launch_gemm_f64(M, Nc, Kd, A, ET_F64, false, lda, B, ET_F64, ldb, C, ldc, stream);
-  const int64_t kchunk = cdiv(cdiv(Kd, P), kMK) * kMK;
-  const int64_t parts = cdiv(Kd, kchunk);
-  if (CRVQ_GEMM_MFMA) {
-    const dim3 gm(static_cast<unsigned>(cdiv(Nc, kMT)), static_cast<unsigned>(cdiv(M, kMT)), static_cast<unsigned>(parts));
-    hipLaunchKernelGGL((gemm_f64_mfma_kernel<false, 4>), gm, dim3(256), 0, stream, M, Nc, Kd, A, lda, B, ldb, ws, Nc,
-                       kchunk, M * Nc);
-  } else {
-    const dim3 grid(static_cast<unsigned>(cdiv(Nc, kGBN)), static_cast<unsigned>(cdiv(M, kGBM)),
-                    static_cast<unsigned>(parts));
-    hipLaunchKernelGGL((gemm_f64_kernel<double, double, false, false>), grid, dim3(256), 0, stream, M, Nc, Kd, A, lda,
-                       B, ldb, ws, Nc, kchunk, M * Nc);
-  }
-  hipLaunchKernelGGL(sum_parts_kernel, dim3(static_cast<unsigned>(cdiv(M * Nc, 256))), dim3(256), 0, stream, M, Nc,
-                     static_cast<int>(parts), ws, C, ldc);
-  return hipGetLastError();
-}
-
 hipError_t launch_row_dot(int64_t M, int64_t n, const double* A, int64_t lda, const double* B, int64_t ldb,
                           double* out, hipStream_t stream) {
   if (M <= 0) return hipSuccess;
@@ -1001,8 +752,8 @@ hipError_t launch_refine_book(int64_t M, int64_t N, int d, int64_t n_cols, doubl
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // the block's code changes reach the later columns: S[:, c0 + bw :] -= D H[c0 .. c0 + bw, c0 + bw :]
     if (c0 + bw < n_cols) {
-      e = launch_gemm_f64(M, n_cols - c0 - bw, bw, D, ET_F64, false, bw_max, H + c0 * ldh + c0 + bw, ET_F64, ldh,
-                          S + c0 + bw, n_cols, stream, true);
+      e = launch_gemm_f64(M, n_cols - c0 - bw, bw, D, bw_max, H + c0 * ldh + c0 + bw, ldh, S + c0 + bw, n_cols, true,
+                          stream);
       if (e != hipSuccess) return e;
     }
   }

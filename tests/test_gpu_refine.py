@@ -381,3 +381,42 @@ def test_refine_loop_lockstep_bf16():
     np.testing.assert_array_equal(tbits(q.C_basic[0].cpu()), ref.books[0])
     assert (tbits(q.C_basic[0].cpu()) != start_books[0]).any()  # the bf16 book did move
     say(f"refine loop bf16: QuantLoss {losses[0]:.6e} -> {losses[-1]:.6e}, {len(trace)} calls matched")
+
+
+@pytest.mark.parametrize("T,N,ld,dtype", [(1, 65, 65, "f32"), (16, 64, 64, "f32"), (17, 128, 130, "f32"),
+                                          (33, 129, 131, "f32"), (40, 200, 200, "f64"), (5, 66, 67, "f64")])
+def test_gram_edges(T, N, ld, dtype):
+    """Tile edges, ragged depth, odd strides and fp64 activations; the proxy is symmetric bit for bit."""
+    say(f"gram {T}x{N} ld {ld} {dtype}")
+    X = np.zeros((T, ld), np.float32 if dtype == "f32" else np.float64)
+    X[:, :N] = rv((T, N), T + N)
+    H = torch.full((N, N + 3), 7.0, dtype=torch.float64, device="cuda")
+    C.crvq_gram(torch.from_numpy(X).cuda()[:, :N], H[:, :N])
+    torch.cuda.synchronize()
+    X64 = X[:, :N].astype(np.float64)
+    got = host(H)
+    assert (np.abs(got[:, :N] - X64.T @ X64) <= TOL * (np.abs(X64).T @ np.abs(X64)) + 1e-300).all()
+    np.testing.assert_array_equal(got[:, :N], got[:, :N].T)
+    assert (got[:, N:] == 7.0).all()
+
+
+@pytest.mark.parametrize("M,N,n_out,off", [(64, 64, 64, 0), (65, 63, 63, 0), (128, 130, 129, 1), (1, 1000, 1, 0),
+                                           # 128 x 128 tiles, a ragged last one
+                                           (4000, 2050, 2050, 0)])
+def test_hessian_product_edges(M, N, n_out, off):
+    """Tile edges of both tile sizes, and rows that do not start at a multiple of 16 bytes."""
+    say(f"hessian product edges {M}x{N} -> {n_out}")
+    g = torch.Generator().manual_seed(M + N)
+    R = torch.randn(M, N + off, generator=g, dtype=torch.float64)[:, off:]
+    H = torch.randn(N, N + off, generator=g, dtype=torch.float64)[:, off:]
+    Gt = torch.full((M, n_out + 1), 5.0, dtype=torch.float64, device="cuda")
+    Rc = torch.empty(M, N + off, dtype=torch.float64, device="cuda")[:, off:]
+    Hc = torch.empty(N, N + off, dtype=torch.float64, device="cuda")[:, off:]
+    Rc.copy_(R)
+    Hc.copy_(H)
+    C.crvq_hessian_product(Rc, Hc, Gt[:, :n_out])
+    torch.cuda.synchronize()
+    got = host(Gt)
+    Rn, Hn = R.numpy(), H.numpy()[:, :n_out]
+    assert (np.abs(got[:, :n_out] - Rn @ Hn) <= TOL * (np.abs(Rn) @ np.abs(Hn)) + 1e-300).all()
+    assert (got[:, n_out:] == 5.0).all()
