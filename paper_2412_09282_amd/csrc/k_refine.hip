@@ -14,6 +14,7 @@
 //    every row, minimising QuantLoss with all other codes fixed; the running product S = R H is
 //    updated in LDS inside the block and, for the later columns, by one product D H per block (D the
 //    block's codeword changes).  One wave per row, eight rows per workgroup.
+//  * refine_rows_kernel: the same for d = 8 and K <= 256, a row's state in its wave's registers.
 #include "crvq_internal.h"
 
 namespace crvq {
@@ -417,6 +418,272 @@ __global__ __launch_bounds__(kRfThreads) void refine_block_kernel(int64_t M, int
   }
 }
 
+// ---- width-1 code search for d = 8 and K <= 256 ----------------------------------------------------
+// The same search with the state of a row in one wave's registers, kRwCols columns per launch.  A lane
+// keeps codewords lane, lane + 64, ... (K <= 256) and columns lane, lane + 64 of the row's R, S = R H and
+// D; the block of H lies in LDS and a_k = c_k^T Hgg c_k comes from a table formed once per call, so a
+// group costs a wave its scores (32 fused multiply-adds per row), an argmin on fp32-rounded keys (the
+// exact values only where several codewords share the least key) and the update of its columns of S,
+// with no barrier.  refine_block_kernel, which forms a_k in every workgroup and meets four barriers
+// per group, took 93 us for 64 columns of 4096 rows; this one takes 40 us for 128: about 10 us until
+// the block of H is in LDS and 2 us per group, where the fp64 issue of the four rows of a SIMD is half.
+// RPW rows per wave share the codewords and the H reads and cover each other's latency.
+constexpr int kRwCols = 128;            // columns per launch
+constexpr int kRwOuter = 512;           // columns between two updates of all later columns of S
+constexpr int kRwStride = kRwCols + 2;  // LDS row stride of H's block: 8 rows of a group on distinct banks
+constexpr int kRwWaves = 8;
+constexpr int kRwK = 256;
+constexpr size_t kRwLds = (kRwCols * kRwStride + kRwK * 8) * sizeof(double);
+
+bool refine_rows_form(int64_t K, int d) { return d == 8 && K <= kRwK; }
+
+// a_k of every group (blockIdx.x) against every codeword; +inf past K, so that a padding codeword is
+// never the minimum.
+__global__ __launch_bounds__(kRwK) void refine_self_kernel(const double* __restrict__ H, int64_t ldh,
+                                                           const void* __restrict__ Cb, int c_type, int K,
+                                                           double* __restrict__ Aself) {
+  __shared__ double Hg[64];
+  const int k = threadIdx.x;
+  const int64_t g = blockIdx.x;
+  if (k < 64) Hg[k] = H[(g * 8 + k / 8) * ldh + g * 8 + k % 8];
+  __syncthreads();
+  double a = __builtin_inf();
+  if (k < K) {
+    double c[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) c[t] = book_elem(Cb, c_type, static_cast<int64_t>(k) * 8 + t);
+    a = 0.0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      double h = 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) h = h + Hg[t * 8 + u] * c[u];
+      a = a + c[t] * h;
+    }
+  }
+  Aself[g * kRwK + k] = a;
+}
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_i32(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+}
+// The minimum over the wave, in every lane.
+__device__ __forceinline__ int wave_min_i32(int v) {
+  v = min(v, dpp_i32<0xB1>(v));   // lane ^ 1
+  v = min(v, dpp_i32<0x4E>(v));   // lane ^ 2
+  v = min(v, dpp_i32<0x141>(v));  // the other four of eight
+  v = min(v, dpp_i32<0x140>(v));  // the other eight of sixteen
+  const auto a = __builtin_amdgcn_permlane16_swap(static_cast<uint32_t>(v), static_cast<uint32_t>(v), false, false);
+  v = min(static_cast<int>(a[0]), static_cast<int>(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(v), static_cast<uint32_t>(v), false, false);
+  return min(static_cast<int>(b[0]), static_cast<int>(b[1]));
+}
+constexpr int kNoKey = 0x7fffffff;
+// f rounded to fp32, as an integer of the same order; kNoKey when that is +inf or NaN.
+__device__ __forceinline__ int order_key(double f) {
+  const float x = static_cast<float>(f);
+  const int u = __float_as_int(x);
+  const int key = u ^ ((u >> 31) & 0x7fffffff);
+  return x < __builtin_inff() ? key : kNoKey;
+}
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(u), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), lane);
+  return __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo);
+}
+
+template <int RPW>
+__global__ __launch_bounds__(64 * kRwWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void refine_rows_kernel(int64_t M, int64_t c0, int bw, double* __restrict__ R,
+                                                                   int64_t ldr, const double* __restrict__ S, int64_t lds,
+                                                                   const double* __restrict__ H, int64_t ldh, int vec,
+                                                                   const void* __restrict__ Cb, int c_type, int K,
+                                                                   int32_t* __restrict__ codes, int64_t ldq,
+                                                                   const double* __restrict__ Aself,
+                                                                   double* __restrict__ D, int64_t ldd) {
+  extern __shared__ double sm[];
+  double* Hb = sm;                         // kRwCols x kRwStride
+  double* Cs = Hb + kRwCols * kRwStride;   // kRwK x 8
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, ng = bw / 8;
+  const int64_t r0 = (static_cast<int64_t>(blockIdx.x) * kRwWaves + w) * RPW, g0 = c0 / 8;
+  // H's block on and right of the diagonal groups; the rest as zeros (those columns take no part, but
+  // every lane updates its columns of S)
+  if (vec && bw == kRwCols) {
+    constexpr int kN = kRwCols * kRwCols / 2 / (64 * kRwWaves);
+    const double2* src = reinterpret_cast<const double2*>(H + c0 * ldh + c0);
+    double2 v[kN];
+#pragma unroll
+    for (int n = 0; n < kN; ++n) {
+      const int i = (tid >> 6) + n * kRwWaves;
+      v[n] = make_double2(0.0, 0.0);
+      if (2 * lane >= (i & ~7)) v[n] = src[i * (ldh / 2) + lane];
+    }
+#pragma unroll
+    for (int n = 0; n < kN; ++n)
+      *reinterpret_cast<double2*>(&Hb[((tid >> 6) + n * kRwWaves) * kRwStride + 2 * lane]) = v[n];
+  } else {
+    for (int e = tid; e < kRwCols * kRwCols; e += 64 * kRwWaves) {
+      const int i = e / kRwCols, j = e % kRwCols;
+      Hb[i * kRwStride + j] = (i < bw && j < bw && j >= (i & ~7)) ? H[(c0 + i) * ldh + c0 + j] : 0.0;
+    }
+  }
+  for (int e = tid; e < kRwK * 8; e += 64 * kRwWaves) Cs[e] = e < K * 8 ? book_elem(Cb, c_type, e) : 0.0;
+  double s[RPW][2], rr[RPW][2], dd[RPW][2];
+  int code[RPW];  // lane g: the code of group g
+#pragma unroll
+  for (int i = 0; i < RPW; ++i) {
+    const int64_t r = r0 + i;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int c = lane + 64 * h;
+      const bool in = r < M && c < bw;
+      s[i][h] = in ? S[r * lds + c0 + c] : 0.0;
+      rr[i][h] = in ? R[r * ldr + c0 + c] : 0.0;
+      dd[i][h] = 0.0;
+    }
+    code[i] = (r < M && lane < ng) ? codes[r * ldq + g0 + lane] : -1;
+  }
+  __syncthreads();
+  double c[4][8];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) c[j][t] = Cs[(lane + 64 * j) * 8 + t];
+  const double* ap = Aself + g0 * kRwK + lane;
+  const int t0 = lane & 7;
+  double an[4];  // a_k of the next group
+#pragma unroll
+  for (int j = 0; j < 4; ++j) an[j] = ap[64 * j];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll 1
+    for (int gi = 0; gi < 8; ++gi) {
+      const int g = 8 * h + gi;
+      if (g >= ng) break;
+      double a[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = an[j];
+      const int gn = g + 1 < ng ? g + 1 : g;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) an[j] = ap[gn * kRwK + 64 * j];
+      __builtin_amdgcn_sched_barrier(0);
+      // the rows go through every stage together, so that one's latency covers the other's
+      int cur[RPW], now[RPW], key[RPW][4], best[RPW];
+      bool valid[RPW];
+      double cc[RPW][8], bt[RPW], b[RPW][8], f[RPW][4];
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) {
+        const int q = __builtin_amdgcn_readlane(code[i], g);
+        valid[i] = static_cast<unsigned>(q) < static_cast<unsigned>(K);
+        cur[i] = valid[i] ? q : 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) cc[i][u] = Cs[cur[i] * 8 + u];
+        bt[i] = s[i][h];
+      }
+      // b = s + Hgg c_cur, element t0 in the group's lane
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double hg = Hb[(8 * g + t0) * kRwStride + 8 * g + u];
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) bt[i] = __builtin_fma(hg, cc[i][u], bt[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) b[i][t] = lane_f64(bt[i], 8 * gi + t);
+#pragma unroll
+      for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[i][j] = c[j][0] * b[i][0];
+#pragma unroll
+      for (int t = 1; t < 8; ++t)
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) f[i][j] = __builtin_fma(c[j][t], b[i][t], f[i][j]);
+#pragma unroll
+      for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          f[i][j] = __builtin_fma(-2.0, f[i][j], a[j]);  // a - 2 dot: the doubling is exact
+          key[i][j] = order_key(f[i][j]);
+        }
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) best[i] = wave_min_i32(min(min(key[i][0], key[i][1]), min(key[i][2], key[i][3])));
+      bool moved = false;
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) {
+        // the codewords whose rounded f is the least (rounding keeps the order, so the minimum is among
+        // them); slot j holds 64 j .. 64 j + 63
+        const int bi = __builtin_amdgcn_readfirstlane(best[i]);
+        uint64_t m[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m[j] = __ballot(key[i][j] == bi);
+        int bk = cur[i];
+        if (bi != kNoKey && __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]) == 1) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) bk = m[j] ? 64 * j + __ffsll(static_cast<long long>(m[j])) - 1 : bk;
+        } else {
+          // several (or f beyond fp32): the exact values in ascending codeword order; +inf and NaN never win
+          double fb = __builtin_inf();
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            uint64_t mj = bi == kNoKey ? __ballot(f[i][j] < __builtin_inf()) : m[j];
+            while (mj) {
+              const int l = __ffsll(static_cast<long long>(mj)) - 1;
+              mj &= mj - 1;
+              const double v = lane_f64(f[i][j], l);
+              if (v < fb) {
+                fb = v;
+                bk = 64 * j + l;
+              }
+            }
+          }
+        }
+        now[i] = valid[i] ? __builtin_amdgcn_readfirstlane(bk) : cur[i];
+        moved = moved || now[i] != cur[i];
+      }
+      if (!moved) continue;
+      double de[RPW][8];
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) {
+        const double* cn = Cs + now[i] * 8;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) de[i][u] = cn[u] - cc[i][u];
+        const double dl = cn[t0] - Cs[cur[i] * 8 + t0];
+        const bool mine = (lane >> 3) == gi;
+        rr[i][h] = mine ? rr[i][h] - dl : rr[i][h];
+        dd[i][h] = mine ? dl : dd[i][h];
+        code[i] = (lane == g && valid[i]) ? now[i] : code[i];
+      }
+      // S of the columns after the group (those up to it are not read again)
+#pragma unroll
+      for (int hh = h; hh < 2; ++hh)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const double hb = Hb[(8 * g + u) * kRwStride + lane + 64 * hh];
+#pragma unroll
+          for (int i = 0; i < RPW; ++i) s[i][hh] = __builtin_fma(-de[i][u], hb, s[i][hh]);
+        }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < RPW; ++i) {
+    const int64_t r = r0 + i;
+    if (r >= M) continue;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int cl = lane + 64 * h;
+      if (cl < bw) {
+        R[r * ldr + c0 + cl] = rr[i][h];
+        D[r * ldd + cl] = dd[i][h];
+      }
+    }
+    if (lane < ng) codes[r * ldq + g0 + lane] = code[i];
+  }
+}
+
 // ---- the same search for books too large for one CU's LDS ------------------------------------------
 // One group at a time over all rows: refine_scan_kernel finds, for 64 rows per workgroup and one slice
 // of the codebook per grid row y, the k minimising f(k) = a_k - 2 c_k . b (the formulas and orders of
@@ -685,13 +952,32 @@ size_t refine_lds_bytes(int64_t K, int d) {
   return static_cast<size_t>(K * d + K + kRbCols * kRbCols + kRfRows * kRbCols) * sizeof(double);
 }
 
+namespace {
+struct RefineWs {
+  double* S;      // M x n_cols: R H on the book's columns
+  double* D;      // M x (columns of an outer block): its codeword changes
+  double* parts;  // the split parts of S
+  double* bestF;  // large books: the slices' minima and codewords
+  int* bestK;
+  double* self;   // d = 8, K <= 256: a_k of every group
+};
+RefineWs carve_refine(WsCursor& c, int64_t M, int64_t n_cols, int64_t N) {
+  RefineWs w;
+  const size_t out = static_cast<size_t>(M) * static_cast<size_t>(n_cols);
+  w.S = c.take<double>(out);
+  w.D = c.take<double>(static_cast<size_t>(M) * kRwOuter);
+  w.parts = c.take<double>(static_cast<size_t>(gemm_split_parts(M, n_cols, N)) * out);
+  w.bestF = c.take<double>(static_cast<size_t>(kRsMaxSlices) * static_cast<size_t>(M));
+  w.bestK = c.take<int>(static_cast<size_t>(kRsMaxSlices) * static_cast<size_t>(M));
+  w.self = c.take<double>(static_cast<size_t>(n_cols / 8) * kRwK);
+  return w;
+}
+}  // namespace
+
 size_t refine_ws_bytes(int64_t M, int64_t n_cols, int64_t N) {
-  return align256(static_cast<size_t>(M) * static_cast<size_t>(n_cols) * sizeof(double)) +
-         align256(static_cast<size_t>(M) * kRbCols * sizeof(double)) +
-         align256(static_cast<size_t>(gemm_split_parts(M, n_cols, N)) * static_cast<size_t>(M) *
-                  static_cast<size_t>(n_cols) * sizeof(double)) +
-         align256(static_cast<size_t>(kRsMaxSlices) * static_cast<size_t>(M) * sizeof(double)) +
-         align256(static_cast<size_t>(kRsMaxSlices) * static_cast<size_t>(M) * sizeof(int));
+  WsCursor c(nullptr);
+  (void)carve_refine(c, M, n_cols, N);
+  return c.used;
 }
 
 // The codebook fits the block kernel's LDS (with H's block and the rows' S).
@@ -702,18 +988,24 @@ hipError_t launch_refine_book(int64_t M, int64_t N, int d, int64_t n_cols, doubl
                               void* ws, hipStream_t stream) {
   if (M <= 0 || n_cols <= 0) return hipSuccess;
   WsCursor cur(ws);
-  double* S = cur.take<double>(static_cast<size_t>(M) * static_cast<size_t>(n_cols));
-  double* D = cur.take<double>(static_cast<size_t>(M) * kRbCols);
-  double* parts = cur.take<double>(static_cast<size_t>(gemm_split_parts(M, n_cols, N)) * static_cast<size_t>(M) *
-                                   static_cast<size_t>(n_cols));
-  double* bestF = cur.take<double>(static_cast<size_t>(kRsMaxSlices) * static_cast<size_t>(M));
-  int* bestK = cur.take<int>(static_cast<size_t>(kRsMaxSlices) * static_cast<size_t>(M));
+  const RefineWs w = carve_refine(cur, M, n_cols, N);
+  double *S = w.S, *D = w.D, *bestF = w.bestF;
+  int* bestK = w.bestK;
   // S = R H[:, 0:n_cols]
-  hipError_t e = launch_gemm_f64_split(M, n_cols, N, R, ldr, H, ldh, S, n_cols, parts, stream);
+  hipError_t e = launch_gemm_f64_split(M, n_cols, N, R, ldr, H, ldh, S, n_cols, w.parts, stream);
   if (e != hipSuccess) return e;
   const size_t lds = refine_lds_bytes(K, d);
   const dim3 grid(static_cast<unsigned>(cdiv(M, kRfRows)));
-  const int64_t bw_max = (kRbCols / d) * d;
+  // d = 8 against K <= 256 keeps the rows in registers (a 4096 x 4096 layer's basic book 10.6 -> 4.85 ms
+  // with the products); other books that fit a CU's LDS are searched from it
+  const bool rows_form = refine_rows_form(K, d);
+  if (rows_form) {
+    hipLaunchKernelGGL(refine_self_kernel, dim3(static_cast<unsigned>(n_cols / 8)), dim3(kRwK), 0, stream, H, ldh, Cb,
+                       c_type, static_cast<int>(K), w.self);
+  }
+  const int rpw = M > 8 * 256 ? 2 : 1;  // two rows per wave once one per wave gives every CU its workgroup
+  const dim3 grid_rows(static_cast<unsigned>(cdiv(M, kRwWaves * rpw)));
+  const int64_t bw_max = rows_form ? kRwCols : (kRbCols / d) * d;
   const bool in_lds = refine_book_in_lds(K, d);
   // large books: enough codebook slices to give the scan about 512 workgroups
   const int64_t row_tiles = cdiv(M, kRsRows);
@@ -722,9 +1014,23 @@ hipError_t launch_refine_book(int64_t M, int64_t N, int d, int64_t n_cols, doubl
   nslice = nslice < cdiv(K, kRsTile) ? nslice : cdiv(K, kRsTile);
   const int slice = static_cast<int>(cdiv(cdiv(K, nslice), kRsTile) * kRsTile);
   nslice = cdiv(K, slice);
+  // S takes a block's code changes D in two steps: right after the block on the columns of its outer
+  // block, S[:, c0 + bw : o1] -= D_block H[block, c0 + bw : o1], and at the outer block's end on all later
+  // columns, S[:, o1 :] -= D H[o0 : o1, o1 :], so that most of S moves once per outer block.
+  const int64_t outer = rows_form ? kRwOuter : bw_max;
+  const int vec = (ldh % 2 == 0 && reinterpret_cast<uintptr_t>(H) % 16 == 0) ? 1 : 0;
   for (int64_t c0 = 0; c0 < n_cols; c0 += bw_max) {
     const int bw = static_cast<int>(n_cols - c0 < bw_max ? n_cols - c0 : bw_max);
-    if (!in_lds) {
+    const int64_t o0 = c0 / outer * outer, o1 = o0 + outer < n_cols ? o0 + outer : n_cols;
+    double* Db = D + (c0 - o0);
+    if (rows_form) {
+      if (rpw == 2)
+        hipLaunchKernelGGL(refine_rows_kernel<2>, grid_rows, dim3(64 * kRwWaves), kRwLds, stream, M, c0, bw, R, ldr, S,
+                           n_cols, H, ldh, vec, Cb, c_type, static_cast<int>(K), codes, ldq, w.self, Db, outer);
+      else
+        hipLaunchKernelGGL(refine_rows_kernel<1>, grid_rows, dim3(64 * kRwWaves), kRwLds, stream, M, c0, bw, R, ldr, S,
+                           n_cols, H, ldh, vec, Cb, c_type, static_cast<int>(K), codes, ldq, w.self, Db, outer);
+    } else if (!in_lds) {
       for (int cg = 0; cg < bw; cg += d) {
         const int64_t gq = c0 / d + cg / d;
         const dim3 gs(static_cast<unsigned>(row_tiles), static_cast<unsigned>(nslice));
@@ -750,12 +1056,12 @@ hipError_t launch_refine_book(int64_t M, int64_t N, int d, int64_t n_cols, doubl
       hipLaunchKernelGGL(refine_block_kernel<16>, grid, dim3(kRfThreads), lds, stream, M, d, c0, bw, R, ldr, S, n_cols,
                          H, ldh, Cb, c_type, static_cast<int>(K), codes, ldq, D, bw_max);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    // the block's code changes reach the later columns: S[:, c0 + bw :] -= D H[c0 .. c0 + bw, c0 + bw :]
-    if (c0 + bw < n_cols) {
-      e = launch_gemm_f64(M, n_cols - c0 - bw, bw, D, bw_max, H + c0 * ldh + c0 + bw, ldh, S + c0 + bw, n_cols, true,
-                          stream);
-      if (e != hipSuccess) return e;
-    }
+    const int64_t c1 = c0 + bw;
+    if (c1 < o1)
+      e = launch_gemm_f64(M, o1 - c1, bw, Db, outer, H + c0 * ldh + c1, ldh, S + c1, n_cols, true, stream);
+    else if (c1 < n_cols)
+      e = launch_gemm_f64(M, n_cols - c1, c1 - o0, D, outer, H + o0 * ldh + c1, ldh, S + c1, n_cols, true, stream);
+    if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }

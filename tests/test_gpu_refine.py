@@ -420,3 +420,38 @@ def test_hessian_product_edges(M, N, n_out, off):
     Rn, Hn = R.numpy(), H.numpy()[:, :n_out]
     assert (np.abs(got[:, :n_out] - Rn @ Hn) <= TOL * (np.abs(Rn) @ np.abs(Hn)) + 1e-300).all()
     assert (got[:, n_out:] == 5.0).all()
+
+
+@pytest.mark.parametrize("M,N,K,n_cols,pad", [(1, 8, 1, 8, 0), (9, 136, 2, 136, 1), (70, 264, 255, 256, 0),
+                                              (33, 1040, 256, 1040, 0), (2049, 64, 65, 64, 0), (2050, 160, 128, 8, 1)])
+def test_refine_codes_rows_form(M, N, K, n_cols, pad):
+    """d = 8 against at most 256 codewords: one and two rows per wave, blocks of 128 columns and outer
+    blocks of 512 with a ragged last one, duplicated codewords (ties go to the lowest), codes outside
+    the book and a row that holds a NaN (left as they are), odd strides of H."""
+    say(f"refine rows form {M}x{N} K={K} cols={n_cols}")
+    R, H, Cb, codes = refine_case(M, N, 8, K, n_cols, "f32", M + K)
+    if K > 4:
+        Cb[K // 2:] = Cb[:K - K // 2]
+    q2 = codes.reshape(M, -1)
+    Rr = R.copy()
+    if M > 4:
+        q2[2, 0], q2[3, -1] = -1, K
+        Rr[4, N - 1] = np.nan
+    Ht = torch.zeros(N, N + pad, dtype=torch.float64, device="cuda")[:, :N]
+    Ht.copy_(torch.from_numpy(H))
+    Rt = torch.from_numpy(Rr.copy()).cuda()
+    qt = dev(codes.copy())
+    C.crvq_refine_codes(Rt, Ht, dev(Cb), qt, 8, n_cols, n_cols // 8)
+    torch.cuda.synchronize()
+    rows = np.array([r for r in range(M) if M <= 4 or r not in (2, 3, 4)])
+    rows = rows if M <= 100 else rows[np.r_[0:20, len(rows) - 20:len(rows)]]
+    Ro, qo = Rr[rows].copy(), q2[rows].copy().ravel()
+    orf.refine_book(Ro, H, Cb, qo, 8, n_cols, "f32")
+    np.testing.assert_array_equal(host(qt).reshape(M, -1)[rows].ravel(), qo)
+    np.testing.assert_array_equal(host(Rt)[rows], Ro)
+    if M > 4:
+        got = host(qt).reshape(M, -1)
+        assert got[2, 0] == -1 and got[3, -1] == K
+        np.testing.assert_array_equal(host(Rt)[2, :8], Rr[2, :8])
+        np.testing.assert_array_equal(got[4], q2[4])
+        np.testing.assert_array_equal(host(Rt)[4], Rr[4])
