@@ -1,77 +1,9 @@
 // fp64 matrix products on the matrix cores: the Hessian proxy H = X^T X, the products R H of the
 // refinement and the rank-k updates of its code search.
-#include "crvq_internal.h"
+#include "f64_tile.h"
 
 namespace crvq {
 namespace {
-
-typedef double d4v __attribute__((ext_vector_type(4)));
-typedef double d2v __attribute__((ext_vector_type(2)));
-typedef float f2v __attribute__((ext_vector_type(2)));
-constexpr int kKs = 16;  // k per LDS stage
-
-__device__ __forceinline__ d2v ld2(const double* p) { return *reinterpret_cast<const d2v*>(p); }
-__device__ __forceinline__ d2v ld2(const float* p) {
-  const f2v v = *reinterpret_cast<const f2v*>(p);
-  return d2v{static_cast<double>(v[0]), static_cast<double>(v[1])};
-}
-
-// One operand tile of `rows` (a multiple of 32) by kKs, staged through LDS as fp64 (fp32 operands are
-// widened exactly).  KMAJ: element (i, k) lies at src[k * ld + i]; otherwise at src[i * ld + k].  The
-// LDS layout keeps the memory order, so a 16-byte load becomes one 16-byte LDS write: k-major with a
-// row stride of 16 mod 32 doubles, row-major with a stride of 18; in both, the 16 rows x 2 k that half a
-// wave reads for an MFMA operand fall on distinct banks.
-template <int ROWS, bool KMAJ, typename T>
-struct Operand {
-  static constexpr int kStride = KMAJ ? ROWS + 16 : kKs + 2;
-  static constexpr int kSize = KMAJ ? kKs * kStride : ROWS * kStride;
-  static constexpr int kLoads = ROWS * kKs / 2 / 256;
-  d2v r[kLoads];
-  // The pair of element (i, k) that load s of thread tid holds (the pair runs along i when KMAJ).
-  static __device__ __forceinline__ void at(int tid, int s, int& i, int& k) {
-    const int e = tid + 256 * s;
-    if (KMAJ) {
-      k = e / (ROWS / 2);
-      i = e % (ROWS / 2) * 2;
-    } else {
-      i = e / (kKs / 2);
-      k = e % (kKs / 2) * 2;
-    }
-  }
-  // src points at the tile's first element; full tiles with 16-byte (fp32: 8-byte) aligned rows
-  __device__ __forceinline__ void fetch(const T* __restrict__ src, int64_t ld, int tid) {
-#pragma unroll
-    for (int s = 0; s < kLoads; ++s) {
-      int i, k;
-      at(tid, s, i, k);
-      r[s] = ld2(src + (KMAJ ? k * ld + i : i * ld + k));
-    }
-  }
-  // any alignment; elements past n_i rows or n_k columns are zero
-  __device__ __forceinline__ void fetch_edge(const T* __restrict__ src, int64_t ld, int64_t n_i, int64_t n_k, int tid) {
-#pragma unroll
-    for (int s = 0; s < kLoads; ++s) {
-      int i, k;
-      at(tid, s, i, k);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int ii = KMAJ ? i + h : i, kk = KMAJ ? k : k + h;
-        r[s][h] = (ii < n_i && kk < n_k) ? static_cast<double>(src[KMAJ ? kk * ld + ii : ii * ld + kk]) : 0.0;
-      }
-    }
-  }
-  __device__ __forceinline__ void store(double* lds, int tid) const {
-#pragma unroll
-    for (int s = 0; s < kLoads; ++s) {
-      int i, k;
-      at(tid, s, i, k);
-      *reinterpret_cast<d2v*>(lds + (KMAJ ? k * kStride + i : i * kStride + k)) = r[s];
-    }
-  }
-  static __device__ __forceinline__ double get(const double* lds, int i, int k) {
-    return lds[KMAJ ? k * kStride + i : i * kStride + k];
-  }
-};
 
 // C[i][j] = sum_k opA(i, k) B(k, j) (C[i][j] - that sum when SUB), opA(i, k) = A[i * lda + k], or
 // A[k * lda + i] when TRANS_A; products exact for fp32 operands, accumulated in k order (within a

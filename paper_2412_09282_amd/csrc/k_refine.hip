@@ -15,7 +15,7 @@
 //    updated in LDS inside the block and, for the later columns, by one product D H per block (D the
 //    block's codeword changes).  One wave per row, eight rows per workgroup.
 //  * refine_rows_kernel: the same for d = 8 and K <= 256, a row's state in its wave's registers.
-#include "crvq_internal.h"
+#include "f64_tile.h"
 
 namespace crvq {
 namespace {
@@ -487,13 +487,6 @@ __device__ __forceinline__ int order_key(double f) {
   const int key = u ^ ((u >> 31) & 0x7fffffff);
   return x < __builtin_inff() ? key : kNoKey;
 }
-__device__ __forceinline__ double lane_f64(double v, int lane) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(u), lane);
-  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), lane);
-  return __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo);
-}
-
 template <int RPW>
 __global__ __launch_bounds__(64 * kRwWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void refine_rows_kernel(int64_t M, int64_t c0, int bw, double* __restrict__ R,
                                                                    int64_t ldr, const double* __restrict__ S, int64_t lds,

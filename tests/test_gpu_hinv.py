@@ -132,3 +132,11 @@ def test_hinv_full_size(wid):
     say(f"hinv full size N {N}: max rel err {rel.max():.3g}")
     assert rel.max() <= 1e-8
     np.testing.assert_array_equal(sc, np.float32(1.0 / (2.0 * got)))
+
+
+@pytest.mark.parametrize("N", [128, 129, 193, 320, 385, 577, 1025])
+def test_hinv_block_counts(N):
+    """Numbers of 64-wide blocks around powers of two: pairs of the doubling with a shorter second block
+    and without one."""
+    rng = np.random.default_rng([2413, N])
+    _check(gram(_calib(rng, N // 2 + 3, N)), 0.01, f"hinv blocks N={N}")
