@@ -351,34 +351,46 @@ crvq_status crvq_assign_residual_beam(const void* X, int x_dtype, int64_t n_rows
   WsCursor c(workspace);
   BeamWs w = carve_beam(c, n, d, n_books, beam, sb);
   const RowSrc src0 = vec_src(X, x_dtype, n_rows, vecs_per_row, ld, d);
-  int64_t n_par = 1;
-  int cur = 0;
-  for (int t = 0; t < n_books; ++t) {
-    const int64_t rows = n * n_par;
-    RowSrc src = src0;
-    if (t > 0) {
-      src.base = w.res[cur];
-      src.type = ET_F64;
-      src.vpr = 1;
-      src.ld = d;
-      src.n = rows;
-    }
-    ScreenPlan p = plan_screen(rows, d, Ks[t], beam);
-    WsCursor sc(w.screen);
-    ScreenWs sw = carve_screen(sc, p, rows, Ks[t]);
-    hipError_t e = launch_screen(src, books[t], book_dtypes[t], Ks[t], beam, p, sw, nullptr, nullptr, w.rowD, w.rowK, st);
-    if (e != hipSuccess) return hip_status(e, fn);
-    e = launch_beam_merge(n, static_cast<int>(n_par), beam, t, n_books, w.rowD, w.rowK, src0, w.res[cur], w.res[cur ^ 1],
-                          w.tup[cur], w.tup[cur ^ 1], w.err, books[t], book_dtypes[t], Ks[t], d, st);
-    if (e != hipSuccess) return hip_status(e, fn);
-    const int64_t nn = n_par * Ks[t];
-    n_par = nn < beam ? nn : beam;
-    cur ^= 1;
-  }
   CodePtrs outs = {};
   for (int t = 0; t < n_books; ++t) {
     outs.q[t] = codes[t];
     outs.ld[t] = ldc ? ldc[t] : vecs_per_row;
+  }
+  int64_t n_par = 1;
+  int cur = 0;
+  for (int t = 0; t < n_books; ++t) {
+    const int64_t nn = n_par * Ks[t], n_next = nn < beam ? nn : beam;
+    hipError_t e;
+    if (beam_small_form(d, Ks[t], n_par, beam)) {
+      // one launch; the residuals only where the next step needs them, and of the last step's children
+      // only the first
+      const bool last = t + 1 == n_books;
+      const bool res = !last && !beam_small_form(d, Ks[t + 1], n_next, beam);
+      e = launch_beam_small(src0, static_cast<int>(n_par), last ? 1 : static_cast<int>(n_next), t, n_books, books,
+                            book_dtypes, Ks[t], w.tup[cur], w.tup[cur ^ 1], res ? w.res[cur ^ 1] : nullptr, last, outs,
+                            vecs_per_row, err, st);
+      if (e != hipSuccess || last) return hip_status(e, fn);
+    } else {
+      const int64_t rows = n * n_par;
+      RowSrc src = src0;
+      if (t > 0) {
+        src.base = w.res[cur];
+        src.type = ET_F64;
+        src.vpr = 1;
+        src.ld = d;
+        src.n = rows;
+      }
+      ScreenPlan p = plan_screen(rows, d, Ks[t], beam);
+      WsCursor sc(w.screen);
+      ScreenWs sw = carve_screen(sc, p, rows, Ks[t]);
+      e = launch_screen(src, books[t], book_dtypes[t], Ks[t], beam, p, sw, nullptr, nullptr, w.rowD, w.rowK, st);
+      if (e != hipSuccess) return hip_status(e, fn);
+      e = launch_beam_merge(n, static_cast<int>(n_par), beam, t, n_books, w.rowD, w.rowK, src0, w.res[cur],
+                            w.res[cur ^ 1], w.tup[cur], w.tup[cur ^ 1], w.err, books[t], book_dtypes[t], Ks[t], d, st);
+      if (e != hipSuccess) return hip_status(e, fn);
+    }
+    n_par = n_next;
+    cur ^= 1;
   }
   return hip_status(launch_beam_emit(n, vecs_per_row, static_cast<int>(n_par), n_books, w.tup[cur], w.err, outs, err, st),
                     fn);

@@ -141,6 +141,14 @@ hipError_t launch_beam_merge(int64_t n, int n_par, int beam, int step, int n_boo
 hipError_t launch_beam_emit(int64_t n, int64_t vpr, int n_par, int n_books, const int* tup, const double* err,
                             const CodePtrs& outs, float* err_out, hipStream_t stream);
 
+// One beam step against a book of at most 256 codewords in one launch (k_beam.hip): types and shapes it
+// takes; parents' residuals come from src0 and the codes in tup_in; res_out (n x n_next x d) may be null;
+// the last step (n_next = 1) writes the codes and errors of the answer.
+bool beam_small_form(int d, int64_t K, int64_t n_par, int beam);
+hipError_t launch_beam_small(const RowSrc& src0, int n_par, int n_next, int step, int n_books, const void* const* C,
+                             const int* types, int64_t K, const int* tup_in, int* tup_out, double* res_out, bool last,
+                             const CodePtrs& outs, int64_t vpr, float* err_out, hipStream_t stream);
+
 // ---- K-means update (k_kmeans.hip) -------------------------------------------------------------
 size_t kmeans_ws_bytes(int64_t n, int64_t K);
 hipError_t launch_kmeans_update(const RowSrc& src, const int32_t* codes, int64_t K, void* C, int c_type,

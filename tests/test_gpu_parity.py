@@ -430,3 +430,57 @@ def test_determinism():
         outs.append([q.cpu().numpy(), Cb.cpu().numpy(), codes[0].cpu().numpy(), codes[1].cpu().numpy()])
     for a, b in zip(*outs):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("beam,Ks,n,d,pad,rows,book", [
+    (8, (256, 256, 256), 1, 8, 0, "f32", "f32"), (8, (255, 17, 16), 333, 8, 0, "bf16", "bf16"),
+    (3, (15, 1, 256), 65, 7, 0, "f32", "f32"), (5, (2, 2, 2, 2, 33), 100, 5, 0, "f32", "f32"),
+    (7, (256, 31), 129, 8, 1, "f32", "bf16"), (1, (256, 100), 47, 4, 0, "bf16", "f32"), (2, (1, 2), 31, 2, 0, "f32", "f32"),
+    (6, (64, 512, 64), 500, 8, 0, "f32", "f32"), (8, (512, 64, 300, 16, 8), 200, 6, 0, "f32", "f32")])
+def test_beam_small_books(beam, Ks, n, d, pad, rows, book):
+    """Books of at most 256 codewords in one launch per step: every parent count, tile remainders, paired
+    and single-element row loads (odd d, odd stride), bf16 rows and books, steps of both kinds in turn."""
+    say(f"beam small books B={beam} Ks={Ks} n={n} d={d} pad={pad} {rows}/{book}")
+    g = np.random.default_rng(n + d)
+    V = rv(n, d, 60)
+    books = [rv(K, d, 61 + t, 0.02 / (2 ** t)) for t, K in enumerate(Ks)]
+    if rows == "bf16":
+        V = inputs.bf16_bits_to_f32(inputs.f32_to_bf16_bits(V))
+    if book == "bf16":
+        books[0] = inputs.bf16_bits_to_f32(inputs.f32_to_bf16_bits(books[0]))
+    Vt = torch.zeros(n, d + pad, dtype=torch.bfloat16 if rows == "bf16" else torch.float32, device="cuda")
+    Vt[:, :d] = torch.from_numpy(V).cuda().to(Vt.dtype)
+    bt = [torch.from_numpy(b).cuda().to(torch.bfloat16 if t == 0 and book == "bf16" else torch.float32)
+          for t, b in enumerate(books)]
+    codes = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in Ks]
+    err = torch.empty(n, dtype=torch.float32, device="cuda")
+    C.crvq_assign_residual_beam(VecSet(Vt, n, 1, d + pad, d), bt, beam, codes, err)
+    torch.cuda.synchronize()
+    exp_codes, exp_err = oracle.beam(V, books, beam)
+    np.testing.assert_array_equal(np.stack([c.cpu().numpy() for c in codes]), exp_codes)
+    np.testing.assert_array_equal(err.cpu().numpy(), exp_err.astype(np.float32))
+
+
+@pytest.mark.parametrize("beam", [1, 2, 4, 8])
+def test_beam_small_books_many_candidates(beam):
+    """More near-equal candidates than a wave keeps (all codewords equal but a few), huge and tiny
+    magnitudes (the screen's bound overflows or vanishes) and NaN rows: exact search, defined codes."""
+    say(f"beam many candidates B={beam}")
+    n, d = 203, 8
+    V = rv(n, d, 70)
+    V[::7] *= np.float32(1e25)
+    V[1::7] *= np.float32(1e-25)
+    b0 = np.repeat(rv(4, d, 71), 64, axis=0)
+    b1 = np.zeros((256, d), np.float32)
+    b1[200:] = rv(56, d, 72, 1e-3)
+    check_beam(V, [b0, b1], beam)
+    Vn = V.copy()
+    Vn[5, 3] = np.nan
+    codes = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(2)]
+    C.crvq_assign_residual_beam(VecSet.of_vectors(dev(Vn)), [dev(b0), dev(b1)], beam, codes)
+    torch.cuda.synchronize()
+    exp, _ = oracle.beam(V, [b0, b1], beam)
+    got = np.stack([c.cpu().numpy() for c in codes])
+    keep = np.arange(n) != 5
+    np.testing.assert_array_equal(got[:, keep], exp[:, keep])
+    assert ((got >= 0) & (got < 256)).all()
