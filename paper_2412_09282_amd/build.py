@@ -24,6 +24,7 @@ ARCH = "gfx950"
 SOURCES = {
     "api.hip": [],
     "k_screen.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "k_small.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "k_beam.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "k_kmeans.hip": [],
     "k_colreduce.hip": [],

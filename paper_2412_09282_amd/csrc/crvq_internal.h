@@ -133,6 +133,10 @@ hipError_t launch_screen(const RowSrc& src, const void* C, int c_type, int64_t K
                          const ScreenWs& w, int32_t* out_codes, float* out_dist, double* rowD, int* rowK,
                          hipStream_t stream);
 
+// Top-1 against K <= 256 codewords in one launch, without scratch (k_small.hip); launch_screen calls it.
+hipError_t launch_assign_small(const RowSrc& src, const void* C, int ct, int64_t K, int32_t* codes, float* dist,
+                               double* rowD, int* rowK, hipStream_t stream);
+
 // Beam bookkeeping kernels.
 hipError_t launch_beam_merge(int64_t n, int n_par, int beam, int step, int n_books, const double* rowD,
                              const int* rowK, const RowSrc& src0, const double* res_in, double* res_out,

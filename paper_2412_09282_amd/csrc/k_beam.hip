@@ -400,31 +400,32 @@ __global__ __launch_bounds__(64 * kBmWaves, 3) void beam_small_kernel(RowSrc src
       const int vv = ((__ffsll(static_cast<long long>(todo)) - 1) & 15) / PP;
       todo &= ~((static_cast<uint64_t>((1u << PP) - 1u) << (vv * PP)) * 0x0001000100010001ull);
       const int64_t iv = ps * V + vv;
-      double pD = -1.0;
+      uint64_t pD = 0;
       int pk = -1;
       for (int s = 0; s < n_next; ++s) {
-        double bD = __builtin_inf();
+        uint64_t bD = kInfBits;
         int bk = INT_MAX;
         for (int e = lane; e < n_par * K; e += 64) {
           const int pp = e / K, k = e - pp * K, key = (pp << 8) | k;
-          const double D = exact(vv * PP + pp, k);
+          const uint64_t D = order_bits(exact(vv * PP + pp, k));
           const bool after = (D > pD) | ((D == pD) & (key > pk));
-          if (after && cless(D, key, bD, bk)) {
+          if (after && (D < bD || (D == bD && key < bk))) {
             bD = D;
             bk = key;
           }
         }
 #pragma unroll
         for (int m = 1; m < 64; m <<= 1) {
-          const double oD = __shfl_xor(bD, m);
+          const uint64_t oD = __shfl_xor(bD, m);
           const int ok = __shfl_xor(bk, m);
-          if (cless(oD, ok, bD, bk)) {
+          if (oD < bD || (oD == bD && ok < bk)) {
             bD = oD;
             bk = ok;
           }
         }
-        const bool none = bk == INT_MAX;  // no distance below +inf (a NaN row): a defined child
-        if (lane == 0) child(iv, vv, s, none ? 0 : bk >> 8, none ? 0 : bk & 255, bD, none);
+        const bool none = bk == INT_MAX;  // no distance left up to +inf (a NaN row): a defined child
+        if (lane == 0)
+          child(iv, vv, s, none ? 0 : bk >> 8, none ? 0 : bk & 255, __builtin_bit_cast(double, bD), none);
         if (!none) {
           pD = bD;
           pk = bk;

@@ -98,6 +98,11 @@ __device__ __forceinline__ void load_codeword(const void* C, int ct, int64_t k, 
     load_bf16_elems<DM>(static_cast<const uint16_t*>(C) + (ok ? k * d : 0), d, ok, c);
 }
 
+// A distance (never below zero) as an integer of the same order; a NaN comes after +inf, also in files
+// compiled without NaN semantics.
+__device__ __forceinline__ uint64_t order_bits(double D) { return __builtin_bit_cast(uint64_t, D); }
+constexpr uint64_t kInfBits = 0x7ff0000000000000ull;
+
 __device__ __forceinline__ bool cless(double Da, int ka, double Db, int kb) {
   return Da < Db || (Da == Db && ka < kb);
 }

@@ -484,3 +484,51 @@ def test_beam_small_books_many_candidates(beam):
     keep = np.arange(n) != 5
     np.testing.assert_array_equal(got[:, keep], exp[:, keep])
     assert ((got >= 0) & (got < 256)).all()
+
+
+@pytest.mark.parametrize("n,d,K,vt,ct,pad", [
+    (1, 8, 256, "f32", "f32", 0), (17, 1, 1, "f32", "f32", 0), (100, 9, 17, "f32", "f32", 0), (1000, 16, 256, "f32", "f32", 0),
+    (33000, 8, 255, "f32", "f32", 0), (33000, 16, 15, "bf16", "bf16", 0), (40000, 12, 100, "bf16", "f32", 0),
+    (262200, 8, 16, "bf16", "bf16", 0), (262200, 8, 256, "f32", "bf16", 0), (270000, 16, 31, "f32", "f32", 0),
+    (50000, 8, 64, "f32", "f32", 1), (262201, 5, 33, "f32", "f32", 0)])
+def test_assign_small_books(n, d, K, vt, ct, pad):
+    """At most 256 codewords, every rows-per-wave form: packed and other layouts, tile remainders, one and
+    two halves of dimensions; near-equal codewords inside and across the cells of four, exact duplicates,
+    rows equal to codewords, with and without distances."""
+    say(f"assign small book n={n} d={d} K={K} {vt}/{ct} pad={pad}")
+    g = np.random.default_rng(n + K)
+    Cb = rv(K, d, 80)
+    if K > 8:
+        Cb[1] = Cb[0] * np.float32(1 + 2e-7)
+        Cb[K - 1] = Cb[2]
+        Cb[5] = Cb[K // 2] + np.float32(1e-9)
+    V = np.ascontiguousarray(np.concatenate([Cb[g.integers(0, K, n // 2)] + rv(n // 2, d, 81, 1e-4), rv(n - n // 2, d, 82)]))
+    if n > 100:
+        V[3:40] = Cb[g.integers(0, K, 37)]
+    Vb, Cbb = (inputs.f32_to_bf16_bits(V) if vt == "bf16" else V), (inputs.f32_to_bf16_bits(Cb) if ct == "bf16" else Cb)
+    Vt, Ct = dev(Vb, vt), dev(Cbb, ct)
+    if pad:
+        wide = torch.zeros(n, d + pad, dtype=Vt.dtype, device="cuda")
+        wide[:, :d] = Vt
+        Vt = wide
+    vs = VecSet(Vt, n, 1, d + pad, d)
+    codes = torch.empty(n, dtype=torch.int32, device="cuda")
+    only = torch.empty(n, dtype=torch.int32, device="cuda")
+    dist = torch.empty(n, dtype=torch.float32, device="cuda")
+    C.crvq_assign(vs, Ct, codes, dist)
+    C.crvq_assign(vs, Ct, only)
+    torch.cuda.synchronize()
+    exp, ed = oracle.assign(Vb, Cbb, vt, ct)
+    np.testing.assert_array_equal(codes.cpu().numpy(), exp)
+    np.testing.assert_array_equal(only.cpu().numpy(), exp)
+    np.testing.assert_array_equal(dist.cpu().numpy(), ed.astype(np.float32))
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-15, 1e18, 1e30])
+def test_assign_small_book_magnitudes(scale):
+    """Screen values that vanish or overflow in fp32: the exact search takes the rows."""
+    say(f"assign small book scale {scale}")
+    V, Cb = rv(500, 8, 83, scale), rv(64, 8, 84, scale)
+    got, _ = run_assign(V, Cb)
+    exp, _ = oracle.assign(V, Cb)
+    np.testing.assert_array_equal(got, exp)
