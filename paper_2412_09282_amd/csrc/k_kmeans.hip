@@ -5,8 +5,8 @@
 // atomics), divided by their count and rounded once to the codebook's type; a codeword without
 // members is left untouched; codes outside [0, K) belong to no cluster.  Only the radix histogram
 // counts with integer LDS atomics.
-// * K <= 256 (small_k_partial): blocks walk contiguous vector ranges; each round of 1024 codes is
-//   bucket-sorted in LDS and thread k adds the members of code k.
+// * K <= 256 (small_k_wave_partial): per-wave tables of sums in LDS; the lanes of a batch of 64 vectors
+//   that share a code find each other with ballots.
 // * K > 256 (bucket_partial8 / bucket_partial): one stable radix pass (per-tile ballot counting,
 //   device-wide scan, stable scatter -- no atomics) groups the vectors by the high byte of their
 //   code; each bucket is then reduced like a small codebook on the low byte, its member vectors
@@ -236,7 +236,7 @@ __device__ __forceinline__ void store_centroid(void* C, int ct, int64_t k, int d
     static_cast<uint16_t*>(C)[k * d + t] = bf16_from_double(v);
 }
 
-// ---- shared by both codebook sizes ---------------------------------------------------------------
+// ---- rounds of the large-codebook reduction ---------------------------------------------------------------
 // A "round" is up to kRound (vector, digit) entries; it is stably bucket-sorted by digit (0..255)
 // in LDS with the ballot multisplit (one leader per digit and batch updates a per-wave counter, so
 // no atomics): afterwards s_pos[s_start[c] .. s_start[c + 1]) lists the round's entries of digit c
@@ -331,72 +331,9 @@ __device__ __forceinline__ void add_vector(const RowSrc& s, int64_t off, double 
     if (t < d) v[t] = v[t] + row_elem(s, off, t);
 }
 
-// ---- small codebooks (K <= 256): one thread per code, no global sort ------------------------------
-// Each block walks a contiguous range of vectors in rounds of kRound.  A round's vectors are staged
-// in LDS with coalesced loads when the set is contiguous and d <= 8; its codes are bucket-sorted and
-// thread k adds the members of code k in ascending order to fp64 accumulators.  The per-block
-// partials (layout [k][t][block]) are folded in block order by one wave per centroid element.
-__global__ __launch_bounds__(256) void small_k_partial(RowSrc src, const int32_t* __restrict__ codes, int64_t K,
-                                                       int64_t per_block, int staged, int64_t nblocks,
-                                                       double* __restrict__ part, int* __restrict__ pcount) {
-  __shared__ RoundLds L;
-  __shared__ float s_vec[kRound * 8];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int d = src.d;
-  const int64_t n = src.n;
-  const int64_t b0 = static_cast<int64_t>(blockIdx.x) * per_block;
-  const int64_t b1 = (b0 + per_block < n) ? b0 + per_block : n;
-  double acc[16];
-#pragma unroll
-  for (int t = 0; t < 16; ++t) acc[t] = 0.0;
-  int cnt = 0;
-  for (int64_t base = b0; base < b1; base += kRound) {
-    const int rn = static_cast<int>((b1 - base) < kRound ? (b1 - base) : kRound);
-    if (staged) {  // vectors base .. base + rn are contiguous: one vector per thread and step
-      for (int v = tid; v < rn; v += 256) {
-        double tmp[16];
-#pragma unroll
-        for (int t = 0; t < 16; ++t) tmp[t] = 0.0;
-        add_vector(src, (base + v) * d, tmp);
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-          if (t < d) s_vec[v * d + t] = static_cast<float>(tmp[t]);
-      }
-    }
-    int dig[kRoundBatches];
-#pragma unroll
-    for (int bt = 0; bt < kRoundBatches; ++bt) {
-      const int e = (w * kRoundBatches + bt) * 64 + lane;
-      const int c = (e < rn) ? codes[base + e] : -1;
-      dig[bt] = (c >= 0 && c < K) ? c : -1;
-    }
-    round_bucket_sort(dig, L);  // ends with a barrier, so s_vec is complete too
-    if (tid < K) {
-      const int e = L.s_start[tid + 1];
-      for (int j = L.s_start[tid]; j < e; ++j) {
-        const int v = L.s_pos[j];
-        if (staged) {
-#pragma unroll
-          for (int t = 0; t < 8; ++t)
-            if (t < d) acc[t] = acc[t] + static_cast<double>(s_vec[v * d + t]);
-        } else {
-          add_vector(src, row_offset(src, base + v), acc);
-        }
-      }
-      cnt += e - L.s_start[tid];
-    }
-    __syncthreads();
-  }
-  if (tid < K) {
-#pragma unroll
-    for (int t = 0; t < 16; ++t)
-      if (t < d) part[(static_cast<int64_t>(tid) * d + t) * nblocks + blockIdx.x] = acc[t];
-    pcount[static_cast<int64_t>(tid) * nblocks + blockIdx.x] = cnt;
-  }
-}
-
-// ---- small codebooks, d <= 8: per-wave tables, no sort ------------------------------------------
-// Every wave owns a private fp64 table of K x 8 sums in LDS and the batches of 64 vectors
+// ---- small codebooks (K <= 256): per-wave tables, no sort ----------------------------------------
+// Dimensions in halves of 8 (blockIdx.y; two at d > 8, where 1 M vectors of 16 take 34 us against 198 us
+// for one thread per code over LDS-sorted rounds).  Every wave owns a private fp64 table of K x 8 sums in LDS and the batches of 64 vectors
 // j = wave, wave + W, wave + 2W, ... (W waves in the grid), so the waves in flight read one moving
 // window of memory.  It reads one vector per lane, kSkDepth batches in flight; within a batch the
 // lanes that share a code find each other with eight ballots, and the lowest of them adds its peers'
@@ -421,13 +358,13 @@ struct SkTable {
   float4 stage[64][2];
 };
 
-// Vector i as 8 floats (zero past d).  KIND 0: fp32 d = 8 with 16-byte aligned vectors (two
-// nontemporal 16-byte loads), KIND 1: bf16 d = 8 aligned (one), KIND 2: element loads (any d <= 8).
+// Elements h0 .. h0 + 7 of vector i as floats (zero past d).  KIND 0: fp32, all eight there and 16-byte
+// aligned (two nontemporal 16-byte loads), KIND 1: bf16 likewise (one), KIND 2: element loads.
 // KIND 0 / 1 are straight-line code: a lane outside the range reads vector 0 (its code is set to
 // -1, so the values are never used), which keeps every prefetched batch in flight.
 template <int KIND>
-__device__ __forceinline__ void sk_load(const RowSrc& s, int64_t i, bool ok, float4& a, float4& b) {
-  const int64_t off = row_offset(s, ok ? i : 0);
+__device__ __forceinline__ void sk_load(const RowSrc& s, int64_t i, int h0, bool ok, float4& a, float4& b) {
+  const int64_t off = row_offset(s, ok ? i : 0) + h0;
   if constexpr (KIND == 0) {
     const float* p = static_cast<const float*>(s.base) + off;
     const uint4 x = ld_stream(p), y = ld_stream(p + 4);
@@ -442,7 +379,7 @@ __device__ __forceinline__ void sk_load(const RowSrc& s, int64_t i, bool ok, flo
   } else {
     float e[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) e[t] = (ok && t < s.d) ? static_cast<float>(row_elem(s, off, t)) : 0.0f;
+    for (int t = 0; t < 8; ++t) e[t] = (ok && h0 + t < s.d) ? static_cast<float>(row_elem(s, off, t)) : 0.0f;
     a = make_float4(e[0], e[1], e[2], e[3]);
     b = make_float4(e[4], e[5], e[6], e[7]);
   }
@@ -456,20 +393,19 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 template <int KIND>
 __global__ __launch_bounds__(64 * kSkWaves) void small_k_wave_partial(RowSrc src, const int32_t* __restrict__ codes,
-                                                                       int64_t K, int64_t per_wave, int64_t nblocks,
+                                                                       int64_t K, int64_t nblocks,
                                                                        double* __restrict__ part,
                                                                        int* __restrict__ pcount) {
   __shared__ SkTable tab[kSkWaves];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   SkTable& T = tab[w];
-  const int d = src.d;
+  const int h0 = blockIdx.y * 8, dh = src.d - h0 < 8 ? src.d - h0 : 8;
   for (int e = lane; e < 256 * 8; e += 64) T.acc[e] = 0.0;
   for (int e = lane; e < 256; e += 64) T.cnt[e] = 0;
   const int64_t n = src.n;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kSkWaves * 64;  // elements between a wave's batches
   const int64_t w0 = (static_cast<int64_t>(blockIdx.x) * kSkWaves + w) * 64;
   const int64_t w1 = n;
-  (void)per_wave;
   // kSkDepth batches in flight: slot s holds batch base + 64 s and is refilled right after use
   // with the batch kSkDepth further on (the loop is unrolled over the slots, so no register holding
   // a pending load is ever copied); a lane's code is masked to -1 only when its batch is used.
@@ -479,7 +415,7 @@ __global__ __launch_bounds__(64 * kSkWaves) void small_k_wave_partial(RowSrc src
   for (int s = 0; s < kSkDepth; ++s) {
     const int64_t i = w0 + stride * s + lane;
     const bool ok = i < w1;
-    sk_load<KIND>(src, i, ok, va[s], vb[s]);
+    sk_load<KIND>(src, i, h0, ok, va[s], vb[s]);
     cq[s] = ld_stream_i32(codes + (ok ? i : 0));
   }
   for (int64_t base = w0; base < w1; base += stride * kSkDepth) {
@@ -514,23 +450,22 @@ __global__ __launch_bounds__(64 * kSkWaves) void small_k_wave_partial(RowSrc src
       }
       const int64_t i = bb + stride * kSkDepth + lane;
       const bool ok = i < w1;
-      sk_load<KIND>(src, i, ok, va[s], vb[s]);
+      sk_load<KIND>(src, i, h0, ok, va[s], vb[s]);
       cq[s] = ld_stream_i32(codes + (ok ? i : 0));
     }
   }
   __syncthreads();
-  for (int64_t e = tid; e < K * d; e += 64 * kSkWaves) {
-    const int64_t k = e / d;
-    const int t = static_cast<int>(e - k * d);
+  for (int e = tid; e < static_cast<int>(K) * dh; e += 64 * kSkWaves) {
+    const int k = e / dh, t = e - k * dh;
     double acc = 0.0;
 #pragma unroll
-    for (int ww = 0; ww < kSkWaves; ++ww) acc = acc + tab[ww].acc[sk_slot(static_cast<int>(k), t)];
-    part[e * nblocks + blockIdx.x] = acc;
-    if (t == 0) {
+    for (int ww = 0; ww < kSkWaves; ++ww) acc = acc + tab[ww].acc[sk_slot(k, t)];
+    part[(static_cast<int64_t>(k) * src.d + h0 + t) * nblocks + blockIdx.x] = acc;
+    if (t == 0 && h0 == 0) {
       int cnt = 0;
 #pragma unroll
       for (int ww = 0; ww < kSkWaves; ++ww) cnt += tab[ww].cnt[k];
-      pcount[k * nblocks + blockIdx.x] = cnt;
+      pcount[static_cast<int64_t>(k) * nblocks + blockIdx.x] = cnt;
     }
   }
 }
@@ -562,29 +497,82 @@ __global__ __launch_bounds__(256) void small_k_final(const double* __restrict__ 
   }
 }
 
-struct SmallPlan {
-  int64_t blocks;
-  int64_t per_block;
-};
+// Few vectors (at most kFewMax): one workgroup per codeword reads all codes, 1024 per wave and step; a wave
+// lists its members in vector order and adds them, eight lanes of dimensions times eight members at a
+// time, lane group j taking the members j, j + 8, ... of every list; the groups are folded by a fixed
+// butterfly and the waves in order.  One launch and no partials: the latency of reading the codes is
+// what it costs (8192 vectors against 256 codewords 5.8 us; the tables and their fold take 6.5 + 3.0 us,
+// 16384: 9.4 against 6.9 + 3.1, where the line lies).
+constexpr int64_t kFewMax = 16384;
+constexpr int kFewStep = 1024;
+constexpr int kFewFlush = 64;            // members listed before they are added
+constexpr int kFewList = kFewFlush + 64;
 
-// The per-wave scheme: one block of kSkWaves waves per CU (LDS holds one block), at most one wave
-// per batch of 64 vectors.
-SmallPlan wave_plan(int64_t n) {
-  SmallPlan p;
-  const int64_t batches = cdiv(n > 0 ? n : 1, 64);
-  const int64_t waves = batches < 256 * kSkWaves ? batches : 256 * kSkWaves;
-  p.blocks = cdiv(waves, kSkWaves);
-  p.per_block = 64;
-  return p;
+__global__ __launch_bounds__(256) void few_vectors_kernel(RowSrc src, const int32_t* __restrict__ codes, void* C, int ct,
+                                                          int32_t* __restrict__ counts) {
+  __shared__ int list_s[4][kFewList];
+  __shared__ double sum_s[4][16];
+  __shared__ int num_s[4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, k = blockIdx.x;
+  int* list = list_s[w];
+  const int n = static_cast<int>(src.n), d = src.d, t = lane & 7, grp = lane >> 3;
+  const uint64_t below = (1ull << lane) - 1ull;
+  double acc0 = 0.0, acc1 = 0.0;  // dimensions t and t + 8
+  int held = 0, total = 0;
+  auto flush = [&]() {
+    wave_lds_sync();
+#pragma unroll 4
+    for (int j = grp; j < held; j += 8) {
+      const int64_t off = row_offset(src, list[j]);
+      if (t < d) acc0 = acc0 + row_elem(src, off, t);
+      if (t + 8 < d) acc1 = acc1 + row_elem(src, off, t + 8);
+    }
+    wave_lds_sync();
+    held = 0;
+  };
+  for (int base = w * kFewStep; base < n; base += 4 * kFewStep) {
+    int c[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int i = base + 64 * q + lane;
+      c[q] = codes[i < n ? i : n - 1];
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const bool mine = c[q] == k && base + 64 * q + lane < n;
+      const uint64_t m = __ballot(mine);
+      if (m) {
+        if (mine) list[held + __popcll(m & below)] = base + 64 * q + lane;
+        held += __popcll(m);
+        total += __popcll(m);
+        if (held > kFewFlush) flush();
+      }
+    }
+  }
+  if (held > 0) flush();
+#pragma unroll
+  for (int m = 8; m < 64; m <<= 1) {
+    acc0 = acc0 + __shfl_xor(acc0, m);
+    acc1 = acc1 + __shfl_xor(acc1, m);
+  }
+  if (grp == 0) {
+    sum_s[w][t] = acc0;
+    sum_s[w][t + 8] = acc1;
+  }
+  if (lane == 0) num_s[w] = total;
+  __syncthreads();
+  const int num = num_s[0] + num_s[1] + num_s[2] + num_s[3], e = threadIdx.x;
+  if (e == 0 && counts) counts[k] = num;
+  if (num > 0 && e < d) {
+    const double sum = sum_s[0][e] + sum_s[1][e] + sum_s[2][e] + sum_s[3][e];
+    store_centroid(C, ct, k, d, e, sum / static_cast<double>(num));
+  }
 }
 
-SmallPlan small_plan(int64_t n) {
-  SmallPlan p;
-  const int64_t rounds = cdiv(n > 0 ? n : 1, kRound);
-  p.blocks = rounds < 2048 ? rounds : 2048;
-  p.per_block = cdiv(rounds, p.blocks) * kRound;
-  p.blocks = cdiv(n > 0 ? n : 1, p.per_block);
-  return p;
+// One block of kSkWaves waves per CU (LDS holds one block), at most one wave per batch of 64 vectors.
+int64_t wave_blocks(int64_t n) {
+  const int64_t batches = cdiv(n > 0 ? n : 1, 64);
+  return cdiv(batches < 256 * kSkWaves ? batches : 256 * kSkWaves, kSkWaves);
 }
 
 // ---- large codebooks (256 < K <= 65536) ----------------------------------------------------------
@@ -894,8 +882,7 @@ hipError_t exclusive_scan(const int* in, int64_t n, int* sums, int* out, int* to
 size_t kmeans_ws_bytes(int64_t n, int64_t K) {
   WsCursor c(nullptr);
   if (K <= 256) {
-    SmallPlan p = small_plan(n), q = wave_plan(n);
-    const int64_t blocks = p.blocks > q.blocks ? p.blocks : q.blocks;
+    const int64_t blocks = wave_blocks(n);
     c.take<double>(static_cast<size_t>(blocks * K * 16));
     c.take<int>(static_cast<size_t>(blocks * K));
     return c.used;
@@ -939,30 +926,32 @@ hipError_t launch_kmeans_update(const RowSrc& src, const int32_t* codes, int64_t
   const int64_t n = src.n;
   WsCursor cur(ws);
   if (K <= 256) {
-    SmallPlan p = small_plan(n), q = wave_plan(n);
-    const int64_t blocks = p.blocks > q.blocks ? p.blocks : q.blocks;
+    const int64_t blocks = wave_blocks(n);
     double* part = cur.take<double>(static_cast<size_t>(blocks * K * 16));
     int* pcount = cur.take<int>(static_cast<size_t>(blocks * K));
-    if (src.d <= 8 && src.type != ET_F64 && n > 0) {
-      const int es = src.type == ET_F32 ? 4 : 2;
-      const bool aligned = src.d == 8 && reinterpret_cast<uintptr_t>(src.base) % 16 == 0 && (src.ld * es) % 16 == 0;
-      const int kind = aligned ? (src.type == ET_F32 ? 0 : 1) : 2;
-      const dim3 g3(static_cast<unsigned>(q.blocks)), b3(64 * kSkWaves);
-      if (kind == 0)
-        hipLaunchKernelGGL(small_k_wave_partial<0>, g3, b3, 0, stream, src, codes, K, q.per_block, q.blocks, part, pcount);
-      else if (kind == 1)
-        hipLaunchKernelGGL(small_k_wave_partial<1>, g3, b3, 0, stream, src, codes, K, q.per_block, q.blocks, part, pcount);
-      else
-        hipLaunchKernelGGL(small_k_wave_partial<2>, g3, b3, 0, stream, src, codes, K, q.per_block, q.blocks, part, pcount);
-      hipLaunchKernelGGL(small_k_final, dim3(static_cast<unsigned>(cdiv(K * src.d, 4))), dim3(256), 0, stream, part,
-                         pcount, q.blocks, K, src.d, C, c_type, counts);
+    // 16-byte loads where every half of every vector starts at one
+    const int es = src.type == ET_F32 ? 4 : 2;
+    const bool aligned = src.d % 8 == 0 && reinterpret_cast<uintptr_t>(src.base) % 16 == 0 && (src.ld * es) % 16 == 0;
+    const int kind = aligned ? (src.type == ET_F32 ? 0 : 1) : 2;
+    if (n > 0 && n <= kFewMax) {
+      hipLaunchKernelGGL(few_vectors_kernel, dim3(static_cast<unsigned>(K)), dim3(256), 0, stream, src, codes, C, c_type,
+                         counts);
       return hipGetLastError();
     }
-    const int staged = (src.ld == src.vpr * src.d) && src.d <= 8;
-    hipLaunchKernelGGL(small_k_partial, dim3(static_cast<unsigned>(p.blocks)), dim3(256), 0, stream, src, codes, K,
-                       p.per_block, staged, p.blocks, part, pcount);
-    hipLaunchKernelGGL(small_k_final, dim3(static_cast<unsigned>(cdiv(K * src.d, 4))), dim3(256), 0, stream, part,
-                       pcount, p.blocks, K, src.d, C, c_type, counts);
+    if (n <= 0) {  // no block may read a vector: the fold of no partials
+      hipLaunchKernelGGL(small_k_final, dim3(static_cast<unsigned>(cdiv(K * src.d, 4))), dim3(256), 0, stream, part,
+                         pcount, int64_t{0}, K, src.d, C, c_type, counts);
+      return hipGetLastError();
+    }
+    const dim3 g3(static_cast<unsigned>(blocks), static_cast<unsigned>(cdiv(src.d, 8))), b3(64 * kSkWaves);
+    if (kind == 0)
+      hipLaunchKernelGGL(small_k_wave_partial<0>, g3, b3, 0, stream, src, codes, K, blocks, part, pcount);
+    else if (kind == 1)
+      hipLaunchKernelGGL(small_k_wave_partial<1>, g3, b3, 0, stream, src, codes, K, blocks, part, pcount);
+    else
+      hipLaunchKernelGGL(small_k_wave_partial<2>, g3, b3, 0, stream, src, codes, K, blocks, part, pcount);
+    hipLaunchKernelGGL(small_k_final, dim3(static_cast<unsigned>(cdiv(K * src.d, 4))), dim3(256), 0, stream, part, pcount,
+                       blocks, K, src.d, C, c_type, counts);
     return hipGetLastError();
   }
   KmWs w = carve(cur, n, K);

@@ -532,3 +532,33 @@ def test_assign_small_book_magnitudes(scale):
     got, _ = run_assign(V, Cb)
     exp, _ = oracle.assign(V, Cb)
     np.testing.assert_array_equal(got, exp)
+
+
+@pytest.mark.parametrize("n,K,d,dtype,pad", [(1, 1, 16, "f32", 0), (16384, 256, 8, "f32", 0), (16385, 256, 16, "f32", 0),
+                                             (5000, 3, 9, "f32", 0), (9000, 17, 16, "bf16", 0), (40000, 256, 16, "bf16", 0),
+                                             (40000, 200, 11, "f32", 0), (20000, 256, 16, "f32", 1)])
+def test_kmeans_update_few_and_wide(n, K, d, dtype, pad):
+    """K <= 256: the one-launch form for few vectors (also one code for most of them) and two halves of
+    dimensions, aligned or not."""
+    say(f"kmeans update few/wide n={n} K={K} d={d} {dtype} pad={pad}")
+    g = np.random.default_rng(n + d)
+    V, C0 = rv(n, d, 90), rv(K, d, 91)
+    codes = g.integers(0, K, n).astype(np.int32)
+    if n > 100:
+        codes[g.random(n) < 0.5] = K // 2
+        codes[3:8] = [-1, K, K + 7, -100, 2 ** 30]
+    if dtype == "bf16":
+        V, C0 = inputs.f32_to_bf16_bits(V), inputs.f32_to_bf16_bits(C0)
+    Vt, Ct = dev(V, dtype), dev(C0, dtype)
+    if pad:
+        wide = torch.zeros(n, d + pad, dtype=Vt.dtype, device="cuda")
+        wide[:, :d] = Vt
+        Vt = wide
+    counts = torch.empty(K, dtype=torch.int32, device="cuda")
+    C.crvq_kmeans_update(VecSet(Vt, n, 1, d + pad, d), dev(codes), Ct, counts)
+    torch.cuda.synchronize()
+    valid = (codes >= 0) & (codes < K)
+    Cexp, cnt, _ = oracle.kmeans_update(V[valid], codes[valid], C0, dtype, dtype)
+    np.testing.assert_array_equal(counts.cpu().numpy(), cnt)
+    rel_close(oracle.widen(to_host_bits(Ct), dtype), oracle.widen(Cexp, dtype), 2.0 ** -23 if dtype == "f32" else 2.0 ** -7,
+              "centroids", axis_vec=True)
