@@ -15,6 +15,7 @@
 // tables are too large, takes direct fp32 dot products), looks up every row's extended codes and
 // writes one more partial per row.  Then y_r = fp64 sum of the partials in order, rounded once.
 // Every sum has a fixed order: results are deterministic.
+// Layers of few rows skip the tables: gemv_rows_kernel takes the dot products row by row in one launch.
 #include "crvq_internal.h"
 
 namespace crvq {
@@ -400,6 +401,156 @@ __device__ void ext_rows(int64_t M, int64_t N, int64_t r0, int64_t r1, int64_t n
   (void)M;
 }
 
+// ---- one pass over the rows, no tables -------------------------------------------------------------
+// A lane keeps the x of 8 consecutive groups (64 columns) in registers, a wave 512 groups, and a row of
+// codes is one 8-byte load per lane; the codewords come from the book in LDS and every group costs its
+// dot product.  The waves of a workgroup are teams of `chunks` waves (512 groups each), a team per row;
+// the team's last wave adds the extended books' items (lane i: book i / ncv, group i % ncv).  No table
+// is built per slice and no partials go through memory: one launch, whose time on the small layers
+// is the chain perm -> x -> LDS -> registers (the first rows' codes travel meanwhile) and a few rows per wave.
+// Sums: 8 terms per group and 8 groups per lane in fp32, the 16 lanes of a DPP row (1024 columns) in
+// fp32, those and the team's waves in fp64, in a fixed order.
+constexpr int kRwThreads = 1024;
+constexpr int kRwRows = 4;      // rows per team whose codes are loaded at once
+constexpr int kRwMaxItems = 2;  // extended items per lane
+constexpr int kRwXPad = 4;      // floats of padding per 64 columns of x in LDS: a lane's reads spread over the banks
+
+__device__ __forceinline__ int64_t rw_x(int64_t col) { return col + (col >> 6) * kRwXPad; }
+
+template <typename TB, typename TX, int ITEMS>
+__global__ __launch_bounds__(kRwThreads) void gemv_rows_kernel(int64_t M, int64_t N, const uint8_t* __restrict__ q_base,
+                                                               int64_t ldq, const TB* __restrict__ C, int K,
+                                                               const int32_t* __restrict__ perm, const TX* __restrict__ x,
+                                                               int chunks, int64_t rows_per_block, int64_t ncv, GemvExt ext,
+                                                               float* __restrict__ y) {
+  extern __shared__ unsigned char smem[];
+  float* xs = reinterpret_cast<float*>(smem);
+  TB* book = reinterpret_cast<TB*>(xs + rw_x(N) + kRwXPad);
+  float* ebook = reinterpret_cast<float*>(book + 256 * 8);
+  double* part = reinterpret_cast<double*>(ebook + static_cast<int64_t>(ext.n) * 256 * 8);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int teams = (kRwThreads / 64) / chunks, team = wave / chunks, chunk = wave - team * chunks;
+  const bool works = team < teams;
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * rows_per_block;
+  const int64_t r1 = r0 + rows_per_block < M ? r0 + rows_per_block : M;
+  const int64_t g0 = static_cast<int64_t>(chunk) * 512 + lane * 8;
+  const bool cols = works && g0 < N / 8;  // N is a multiple of 64
+  const int items = works && chunk == chunks - 1 ? static_cast<int>(ext.n * ncv) : 0;
+  int ie[ITEMS + 1], ig[ITEMS + 1];  // (one more: ITEMS may be 0)
+#pragma unroll
+  for (int s = 0; s < ITEMS; ++s) {
+    const int it = lane + 64 * s;
+    ie[s] = it < items ? it / static_cast<int>(ncv) : -1;
+    ig[s] = it < items ? it - ie[s] * static_cast<int>(ncv) : 0;
+  }
+  uint2 q[kRwRows];
+  int qe[kRwRows][ITEMS + 1];
+  auto load = [&](int64_t rb) {
+#pragma unroll
+    for (int u = 0; u < kRwRows; ++u) {
+      const int64_t r = rb + static_cast<int64_t>(u) * teams + team;
+      q[u] = cols && r < r1 ? ld_stream8(q_base + r * ldq + g0) : make_uint2(0u, 0u);
+#pragma unroll
+      for (int s = 0; s < ITEMS; ++s)
+        qe[u][s] = ie[s] >= 0 && r < r1 ? ext.q[ie[s]][r * ext.ldq + ig[s]] : 0;
+    }
+  };
+  load(r0);
+  for (int64_t c = tid; c < N; c += kRwThreads) {
+    const int64_t src = perm ? static_cast<int64_t>(perm[c]) : c;
+    xs[rw_x(c)] = src >= 0 && src < N ? elem_f(x, src) : __builtin_nanf("");  // makes every row NaN
+  }
+  for (int e = tid; e < K * 8; e += kRwThreads) book[e] = C[e];
+  for (int b = 0; b < ext.n; ++b)
+    for (int e = tid; e < ext.K[b] * 8; e += kRwThreads)
+      ebook[b * 2048 + e] = ext.type[b] == ET_F32 ? elem_f(static_cast<const float*>(ext.C[b]), e)
+                                                  : elem_f(static_cast<const uint16_t*>(ext.C[b]), e);
+  __syncthreads();
+  float xr[64];
+#pragma unroll
+  for (int t = 0; t < 16; ++t) {
+    const float4 v = cols ? *reinterpret_cast<const float4*>(xs + rw_x(g0 * 8) + 4 * t) : make_float4(0.f, 0.f, 0.f, 0.f);
+    xr[4 * t] = v.x;
+    xr[4 * t + 1] = v.y;
+    xr[4 * t + 2] = v.z;
+    xr[4 * t + 3] = v.w;
+  }
+  const int64_t step = static_cast<int64_t>(teams) * kRwRows;
+  for (int64_t rb = r0; rb < r1; rb += step) {
+    double sum[kRwRows];
+#pragma unroll
+    for (int u = 0; u < kRwRows; ++u) {
+      sum[u] = 0.0;
+      if (rb + static_cast<int64_t>(u) * teams + team >= r1) continue;  // uniform in the wave
+      float s = 0.0f;
+      bool bad = false;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int code = static_cast<int>(((j < 4 ? q[u].x : q[u].y) >> (8 * (j & 3))) & 255u);
+        float c[8];
+        codeword8(book, code, c);
+        float a = c[0] * xr[8 * j];
+#pragma unroll
+        for (int t = 1; t < 8; ++t) a = fmaf(c[t], xr[8 * j + t], a);
+        s += a;
+        bad = bad || code >= K;
+      }
+      bad = bad && cols;
+      if (!cols) s = 0.0f;  // (entry 0 of the book times zero, but the book may hold anything)
+      if (ITEMS > 0 && items > 0) {
+#pragma unroll
+        for (int t = 0; t < ITEMS; ++t) {
+          if (ie[t] >= 0) {
+            const int code = qe[u][t];
+            const bool in = code < ext.K[ie[t]];
+            const float* c = ebook + ie[t] * 2048 + (in ? code : 0) * 8;
+            const float* xv = xs + rw_x(static_cast<int64_t>(ig[t]) * 8);
+            float a = c[0] * xv[0];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) a = fmaf(c[e], xv[e], a);
+            s += a;
+            bad = bad || !in;
+          }
+        }
+      }
+      if (bad) s = __builtin_nanf("");
+      s = row16_sum(s);
+      // lanes 0, 16, 32, 48 hold the four rows' sums of 1024 columns
+      const double d0 = static_cast<double>(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), 0)));
+      const double d1 = static_cast<double>(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), 16)));
+      const double d2 = static_cast<double>(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), 32)));
+      const double d3 = static_cast<double>(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), 48)));
+      sum[u] = ((d0 + d1) + d2) + d3;
+    }
+    load(rb + step);  // past the range: nothing is read
+    if (chunks == 1) {
+      double v = sum[0];
+#pragma unroll
+      for (int u = 1; u < kRwRows; ++u) v = lane == u ? sum[u] : v;
+      const int64_t r = rb + static_cast<int64_t>(lane) * teams + team;
+      if (lane < kRwRows && r < r1) y[r] = static_cast<float>(v);
+    } else {
+      if (works && lane == 0) {
+#pragma unroll
+        for (int u = 0; u < kRwRows; ++u) part[(u * teams + team) * chunks + chunk] = sum[u];
+      }
+      __syncthreads();
+      if (tid < teams * kRwRows && rb + tid < r1) {
+        double v = 0.0;
+        for (int c = 0; c < chunks; ++c) v += part[tid * chunks + c];
+        y[rb + tid] = static_cast<float>(v);
+      }
+      __syncthreads();
+    }
+  }
+}
+
+size_t gemv_rows_lds(int64_t N, int base_size, int n_ext) {
+  const int64_t x = N + N / 64 * kRwXPad + kRwXPad;
+  return static_cast<size_t>(x) * 4 + 2048 * static_cast<size_t>(base_size) + 8192 * static_cast<size_t>(n_ext) +
+         (kRwThreads / 64) * kRwRows * sizeof(double);
+}
+
 // Finish: y_r = fp64 sum of the partials [0, n_part) in order, rounded once.
 __global__ __launch_bounds__(256) void gemv_reduce_kernel(int64_t M, int n_part, const float* __restrict__ part,
                                                           float* __restrict__ y) {
@@ -471,6 +622,40 @@ hipError_t launch_gemv(int64_t M, int64_t N, int64_t n_crit, const uint8_t* q_ba
   int ext_K_sum = 0;
   for (int e = 0; e < ext.n; ++e) ext_K_sum += ext.K[e];
   const GemvPlan p = plan_gemv(M, N, K_base, has_ext ? ncv : 0, has_ext ? ext_K_sum : 0, has_ext ? ext.n : 0);
+  // The one-pass form costs M (chunks + extended items per lane) row visits of a wave, an fp32 book a
+  // quarter more for its wider reads; the tables cost two launches and their build whatever M.  Measured
+  // (bf16, one-pass against tables): 4096 x 4096 6.1 / 15.9 us, 11008 x 4096 + 1 book 10.9 / 15.6 (22016
+  // visits), 13824 x 5120 13.6 / 19.0 (27648), 13824 x 5120 + 3 books 21.2 / 16.5 (41472), 28672 x 8192 + 1
+  // 37 / 28; fp32: 11008 x 4096 + 1 13.8 / 16.0, 8192 x 8192 + 1 19.1 / 18.7 (30720).  Four and more
+  // chunks leave few teams per workgroup (5120 x 13824 + 1 fp32 25 / 20).
+  const int chunks = static_cast<int>(cdiv(N / 8, 512));
+  const int per_lane = has_ext ? static_cast<int>(cdiv(ext.n * ncv, 64)) : 0;
+  const double visits = static_cast<double>(M) * (chunks + per_lane) * (base_type == ET_F32 ? 1.25 : 1.0);
+  const size_t rows_lds = gemv_rows_lds(N, base_type == ET_F32 ? 4 : 2, has_ext ? ext.n : 0);
+  if (chunks <= 3 && per_lane <= kRwMaxItems && visits <= 30000.0 && rows_lds <= 160 * 1024) {
+    GemvExt used = ext;
+    if (!has_ext) used.n = 0;
+    const int teams = (kRwThreads / 64) / chunks;
+    const int64_t blocks = cdiv(M, teams) < 256 ? cdiv(M, teams) : 256, rows = cdiv(M, blocks);
+#define CRVQ_GEMV_ROWS_I(TB, TX, I)                                                                                   \
+  hipLaunchKernelGGL((gemv_rows_kernel<TB, TX, I>), dim3(static_cast<unsigned>(cdiv(M, rows))), dim3(kRwThreads), rows_lds, \
+                     stream, M, N, q_base, ldq_base, static_cast<const TB*>(C_base), K_base, perm,                    \
+                     static_cast<const TX*>(x), chunks, rows, ncv, used, y)
+#define CRVQ_GEMV_ROWS(TB, TX)                          \
+  do {                                                  \
+    if (per_lane == 0) CRVQ_GEMV_ROWS_I(TB, TX, 0);     \
+    else if (per_lane == 1) CRVQ_GEMV_ROWS_I(TB, TX, 1); \
+    else CRVQ_GEMV_ROWS_I(TB, TX, 2);                   \
+  } while (0)
+    if (base_type == ET_F32) {
+      if (x_type == ET_F32) CRVQ_GEMV_ROWS(float, float); else CRVQ_GEMV_ROWS(float, uint16_t);
+    } else {
+      if (x_type == ET_F32) CRVQ_GEMV_ROWS(uint16_t, float); else CRVQ_GEMV_ROWS(uint16_t, uint16_t);
+    }
+#undef CRVQ_GEMV_ROWS
+#undef CRVQ_GEMV_ROWS_I
+    return hipGetLastError();
+  }
   float* part = static_cast<float*>(ws);
   const int n_part = p.n_slices + (has_ext ? 1 : 0);
   const dim3 grid(static_cast<unsigned>(p.n_slices + p.ext_cols), static_cast<unsigned>(p.row_blocks));

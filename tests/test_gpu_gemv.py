@@ -99,3 +99,31 @@ def test_gemv_empty_and_bad_codes():
     codes[0][3 * (N // 8) + 5] = 0
     exp, a = oracle.gemv(M, N, 8, 16, codes, books, perm, x)
     assert (np.abs(got[ok] - exp[ok]) <= TOL * a[ok]).all()
+
+
+@pytest.mark.parametrize("M,N,n_crit,n_ext,K_base,K_ext,dtype,perm", [
+    (1, 4096, 96, 7, 256, 256, "bf16", True),       # one row, two extended items per lane
+    (17, 4160, 88, 1, 256, 256, "f32", True),       # a second wave of columns, nearly empty
+    (300, 12288, 128, 2, 200, 31, "bf16", True),    # three waves per row
+    (5000, 64, 64, 1, 3, 256, "f32", False),        # every group critical, eight lanes at work
+    (4103, 8192, 0, 0, 256, 256, "bf16", True),     # ragged rows over full workgroups
+    # table forms: many rows, short books, extended tables that fit and that do not
+    (30011, 256, 40, 3, 100, 7, "f32", True), (15011, 512, 512, 2, 256, 256, "bf16", True),
+    (31003, 128, 0, 0, 16, 16, "f32", False), (600, 16448, 88, 1, 256, 256, "bf16", True)])
+def test_gemv_forms(M, N, n_crit, n_ext, K_base, K_ext, dtype, perm):
+    """The one-pass form's edges, and the table forms at sizes that still take them."""
+    check(M, N, n_crit, n_ext, K_base, K_ext, dtype, 500 + M, perm)
+
+
+def test_gemv_rows_bad_entries():
+    """One-pass form: an extended code outside its book makes its row NaN, a perm entry outside the
+    columns every row."""
+    M, N = 50, 4096
+    books, codes, perm, x = make_layer(M, N, 88, 2, 256, 100, "f32", 78)
+    codes[2][7 * 11 + 3] = 120
+    got, _ = run_gemv(M, N, 88, books, codes, perm, x, "f32")
+    assert np.isnan(got[7]) and np.isfinite(np.delete(got, 7)).all()
+    codes[2][7 * 11 + 3] = 0
+    perm[4000] = N
+    got, _ = run_gemv(M, N, 88, books, codes, perm, x, "f32")
+    assert np.isnan(got).all()
