@@ -36,6 +36,8 @@ class CrvqError(RuntimeError):
 def lib(build_if_missing: bool = True):
     """Load libcrvq.so (building it first only if no built library exists)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -92,7 +94,7 @@ def lib(build_if_missing: bool = True):
                 f = getattr(L, name)
                 f.argtypes = args
                 f.restype = res
-            _lib = L
+            _lib = L  # last: a caller that sees it finds every signature set
     return _lib
 
 
@@ -100,24 +102,27 @@ def lib(build_if_missing: bool = True):
 # marshalling helpers
 # ------------------------------------------------------------------------------------------------
 
+_DTYPE_CODES = {torch.float32: CRVQ_F32, torch.bfloat16: CRVQ_BF16, torch.float64: CRVQ_F64}
+
+
 def dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return CRVQ_F32
-    if t.dtype == torch.bfloat16:
-        return CRVQ_BF16
-    if t.dtype == torch.float64:
-        return CRVQ_F64
-    raise TypeError(f"unsupported element type {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported element type {t.dtype}")
+    return code
 
 
+# Pointers and streams go to ctypes as plain integers (its c_void_p arguments take them; None is NULL).
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        # the current device's current stream, without the Stream object torch.cuda.current_stream() makes
+        # (a call on a small layer costs less on the GPU than that)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(fn: str, status: int):
