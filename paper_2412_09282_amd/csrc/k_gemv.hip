@@ -408,7 +408,7 @@ __device__ void ext_rows(int64_t M, int64_t N, int64_t r0, int64_t r1, int64_t n
 // the team's last wave adds the extended books' items (lane i: book i / ncv, group i % ncv).  No table
 // is built per slice and no partials go through memory: one launch, whose time on the small layers
 // is the chain perm -> x -> LDS -> registers (the first rows' codes travel meanwhile) and a few rows per wave.
-// Sums: 8 terms per group and 8 groups per lane in fp32, the 16 lanes of a DPP row (1024 columns) in
+// Sums: 8 terms per group and, in pairs, 8 groups per lane in fp32, the 16 lanes of a DPP row (1024 columns) in
 // fp32, those and the team's waves in fp64, in a fixed order.
 constexpr int kRwThreads = 1024;
 constexpr int kRwRows = 4;      // rows per team whose codes are loaded at once
@@ -482,19 +482,19 @@ __global__ __launch_bounds__(kRwThreads) void gemv_rows_kernel(int64_t M, int64_
     for (int u = 0; u < kRwRows; ++u) {
       sum[u] = 0.0;
       if (rb + static_cast<int64_t>(u) * teams + team >= r1) continue;  // uniform in the wave
-      float s = 0.0f;
+      float p[8];
       bool bad = false;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int code = static_cast<int>(((j < 4 ? q[u].x : q[u].y) >> (8 * (j & 3))) & 255u);
         float c[8];
         codeword8(book, code, c);
-        float a = c[0] * xr[8 * j];
+        p[j] = c[0] * xr[8 * j];
 #pragma unroll
-        for (int t = 1; t < 8; ++t) a = fmaf(c[t], xr[8 * j + t], a);
-        s += a;
+        for (int t = 1; t < 8; ++t) p[j] = fmaf(c[t], xr[8 * j + t], p[j]);
         bad = bad || code >= K;
       }
+      float s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
       bad = bad && cols;
       if (!cols) s = 0.0f;  // (entry 0 of the book times zero, but the book may hold anything)
       if (ITEMS > 0 && items > 0) {
