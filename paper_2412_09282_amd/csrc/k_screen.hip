@@ -50,9 +50,6 @@
 #ifndef CRVQ_S32_SCREEN
 #define CRVQ_S32_SCREEN 1  // 32 x 32 split-fp16 tiles for long top-1 searches
 #endif
-#ifndef CRVQ_S32_MIN_TILES
-#define CRVQ_S32_MIN_TILES 256  // 16-codeword tiles per split from which the 32 x 32 screen is used
-#endif
 #ifndef CRVQ_S32_CB
 #define CRVQ_S32_CB 4  // 32-row column blocks per wave
 #endif
@@ -604,6 +601,12 @@ constexpr int kS32Tile = 32;         // codewords per tile
 constexpr int64_t kRescueBlocks = 1024;  // persistent grid of the exact rescue
 constexpr int kRescueParts = 16;         // codeword ranges of a parted top-1 rescue
 constexpr int64_t kRescuePartMinK = 8192;  // codebooks from which the top-1 rescue is parted
+// The 32 x 32 screen costs more launches than the 16 x 16 one; us, fp32 rows, 16 x 16 / 32 x 32: K = 2048 x
+// 262,144 rows 101 / 90, 4096 x 65,536 72 / 82 and x 131,072 108 / 94, 8192 x 65,536 109 / 92; K = 1024 stays below
+// at any length (x 2 M 275 / 321).
+constexpr int64_t kS32MinK = 2048;
+constexpr int64_t kS32MinPairs = 500000000;      // rows x codewords
+constexpr int64_t kS32DirectPairs = 3000000000;  // unpruned: below, every row takes the split form at once
 constexpr int64_t kS32SharedRowsMaxN = int64_t{1} << 23;  // second screen: shared rows below this n
 constexpr int kS32TileHalves = 768;  // packed fp16 per tile: c1, c2, N terms, 32 x 8 each
 constexpr int kS32MaxParts = 256;    // partial maxima of the codebook scale reduction
@@ -627,7 +630,12 @@ constexpr int kPruneBins2 = 16;                // bins of coordinate j (middle k
 constexpr int kPruneBins3 = 64;                // bins of coordinate q (minor key)
 constexpr int kPruneKeys = kPruneBins1 * kPruneBins2 * kPruneBins3;
 constexpr int kPruneFine = 4096;               // fine bins of each key feature (quantile edges)
-constexpr int64_t kPruneMinRows = 32768;       // rows from which the screen is pruned
+// Pruning orders the rows and walks chunks out of sequence, which pays for itself once whole searches are
+// long: measured pruned / unpruned in us (fp32 rows), K = 4096 x 2 M rows 764 / 532, 8192 x 2 M 952 / 763,
+// 16384 x 1 M 768 / 680 and x 2 M 1280 / 1277, 32768 x 0.7 M 843 / 908 and x 2 M 1869 / 2292,
+// 65536 x 0.4 M 1001 / 1018 and x 2 M 2802 / 4424.
+constexpr int64_t kPruneMinK = 16384;
+constexpr int64_t kPruneMinPairs = 25000000000;  // rows x codewords
 
 struct PruneData {
   const int* corder;        // sorted codeword position -> codeword
@@ -2875,31 +2883,46 @@ ScreenPlan plan_screen(int64_t n_rows, int d, int64_t K, int top) {
   p.tiles = cdiv(K, 16);
   p.grid_x = cdiv(n_rows, 64 * p.cb);
   int64_t splits = 1;
+  // Long top-1 searches: 32 x 32 split-fp16 tiles (two MFMAs per 1024 values instead of four).
+  const bool s32 = p.split && CRVQ_S32_SCREEN && p.nb == 1 && K >= kS32MinK && n_rows * K >= kS32MinPairs;
   const int64_t want_blocks = 2048;
-  if (p.grid_x < want_blocks) {
+  p.prune = 0;
+  if (s32) {
+    // Two workgroups of 32 x 32 tiles are resident per CU: rows that fill them are not split, since every
+    // split scores its own winners exactly (4096 codewords x 386,625 rows: 185 us in three splits,
+    // 177 in one).  A last wave that is nearly empty costs long books more than that: 16384 codewords and
+    // more per split then (32768 x 270,000 rows: 511 us in one).
+    const int64_t fill = 512 / (p.grid_x > 0 ? p.grid_x : 1), tail = cdiv(want_blocks, p.grid_x);
+    const int64_t most = K / 16384;
+    splits = tail < most ? tail : most;
+    splits = splits > fill ? splits : fill;
+    const int64_t maxs = p.tiles / 32 > 1 ? p.tiles / 32 : 1;
+    splits = splits < 1 ? 1 : (splits < maxs ? splits : maxs);
+    // many rows: codebook and rows in key order, chunks of two tiles skipped when certified useless
+    // (only without codebook splits: a split would see a slice of the key order and prune little)
+    if (CRVQ_PRUNE && CRVQ_S32_CHUNK == 2 && K >= kPruneMinK && n_rows * K >= kPruneMinPairs && p.grid_x >= 512) {
+      p.prune = 1;
+      splits = 1;
+    }
+  } else if (p.grid_x < want_blocks) {
     int64_t want = cdiv(want_blocks, p.grid_x > 0 ? p.grid_x : 1);
     int64_t maxs = p.tiles / 32 > 1 ? p.tiles / 32 : 1;
     splits = want < maxs ? want : maxs;
   }
   // small codebooks cannot be split further: spread the rows over more, smaller workgroups instead
-  if (p.grid_x * splits < 1024 && p.nb <= 2) {
+  if (!s32 && p.grid_x * splits < 1024 && p.nb <= 2) {
     p.cb = 2;
     p.grid_x = cdiv(n_rows, 64 * p.cb);
   }
   p.tiles_per_split = cdiv(p.tiles, splits);
   p.splits = static_cast<int>(cdiv(p.tiles, p.tiles_per_split));
   p.chunk = (p.tiles_per_split >= CRVQ_CHUNK_MIN_TILES && p.nb <= 8) ? (p.nb == 1 ? CRVQ_CHUNK : CRVQ_CHUNK_TOPB) : 1;
-  // Long top-1 searches: 32 x 32 split-fp16 tiles (two MFMAs per 1024 values instead of four).
-  // The same rows per workgroup and codebook splits, counted in 32-codeword tiles.
-  p.s32 = (p.split && CRVQ_S32_SCREEN && p.nb == 1 && p.tiles_per_split >= CRVQ_S32_MIN_TILES) ? 1 : 0;
-  p.prune = 0;
+  p.s32 = s32 ? 1 : 0;
   if (p.s32) {
+    // the same rows per workgroup and codebook splits, counted in 32-codeword tiles
     p.cb = CRVQ_S32_CB;
     p.grid_x = cdiv(n_rows, 128 * p.cb);
     p.tiles = cdiv(K, kS32Tile);
-    // many rows: codebook and rows in key order, chunks of two tiles skipped when certified useless
-    // (only without codebook splits: a split would see a slice of the key order and prune little)
-    p.prune = (CRVQ_PRUNE && CRVQ_S32_CHUNK == 2 && splits == 1 && n_rows >= kPruneMinRows) ? 1 : 0;
     if (p.prune) p.tiles += p.tiles & 1;  // whole chunks; a padding tile never wins
     p.tiles_per_split = cdiv(p.tiles, splits);
     if (p.prune) p.tiles_per_split += p.tiles_per_split & 1;
@@ -3046,6 +3069,23 @@ hipError_t launch_screen(const RowSrc& src, const void* C, int ct, int64_t K, in
     if ((e = hipGetLastError()) != hipSuccess) return e;
     dim3 grid(static_cast<unsigned>(p.grid_x), static_cast<unsigned>(p.splits));
     const bool exact = s32_exact_operands(src.type, ct);
+    // Exact operands need one MFMA per tile and no second screen.  Other operands take the split form at
+    // once where the list screen's launches cost more than the second MFMA (fp32 rows, split form at once /
+    // two screens: K = 4096 x 131,072 rows 94 / 134 us, x 386,625 152 / 177, x 800,000 282 / 275; K = 16384 x
+    // 131,072 181 / 198).
+    if (!p.prune && (exact || src.n * K < kS32DirectPairs)) {
+      if (exact)
+        hipLaunchKernelGGL((screen32_kernel<CRVQ_S32_CB, CRVQ_S32_CHUNK, true, false>), grid, dim3(256), 0, stream, src,
+                           ap, alpha, p.tiles, p.tiles_per_split, C, ct, K, w.pR, w.pD, w.pK, w.xn2, nullptr, nullptr,
+                           nullptr, nullptr, pd, 0.0, 0.0);
+      else
+        hipLaunchKernelGGL((screen32_kernel<CRVQ_S32_CB, CRVQ_S32_CHUNK, false, false>), grid, dim3(256), 0, stream, src,
+                           ap, alpha, p.tiles, p.tiles_per_split, C, ct, K, w.pR, w.pD, w.pK, w.xn2, nullptr, nullptr,
+                           nullptr, nullptr, pd, 0.0, 0.0);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      const ScreenBound bound = screen_bound(p, src.type, ct, src.d, alpha);
+      return launch_finalize_ks<2>(src, C, ct, K, top, p, w, bound, out_codes, out_dist, rowD, rowK, stream);
+    }
     // First screen: one MFMA per tile.  Exact for bf16 rows against a bf16 book; otherwise on
     // fp16-rounded operands, certified with the wider bound.
     // (fp16-rounded operands: each row's own split term, from the screen, replaces the worst case)
@@ -3061,10 +3101,6 @@ hipError_t launch_screen(const RowSrc& src, const void* C, int ct, int64_t K, in
                          ap, alpha, p.tiles, p.tiles_per_split, C, ct, K, w.pR, w.pD, w.pK, w.xn2, xe, nullptr, nullptr,
                          nullptr, pd, 0.0, 0.0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (exact && !p.prune) {
-      const ScreenBound bound = screen_bound(p, src.type, ct, src.d, alpha);
-      return launch_finalize_ks<2>(src, C, ct, K, top, p, w, bound, out_codes, out_dist, rowD, rowK, stream);
-    }
     if (exact) {
       // results at key-order positions: certify by position, compact the uncertain rows, rescue them
       const int64_t nbx = cdiv(src.n, 256);

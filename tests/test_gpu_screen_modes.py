@@ -1,9 +1,8 @@
 """GPU parity of the nearest-codeword search on the shapes that select each screen variant.
 
-Long top-1 searches (at least 256 16-codeword tiles per codebook split, e.g. 65536 rows x 65536
-codewords) run on 32 x 32 tiles under a power-of-two codebook scale: one fp16 MFMA per tile, exact for
+Long top-1 searches (at least 2048 codewords and 5e8 pairs of a row and a codeword) run on 32 x 32 tiles under a power-of-two codebook scale: one fp16 MFMA per tile, exact for
 bf16 operands, and for fp32 operands a second, split-fp16 screen of the rows the first leaves
-uncertain; shorter ones on 16 x 16 tiles with split-bf16 operands.  Whatever the variant, the certified screen plus the
+uncertain (the split form at once below 3e9 pairs); shorter ones on 16 x 16 tiles with split-bf16 operands.  Whatever the variant, the certified screen plus the
 exact rescue must return the oracle's codes (the fp64 definition of Eq. 3, ties to the lower index)
 and its distances, including rows the scaled screen cannot represent (forced to the exact rescue),
 codebooks of extreme magnitude and ragged tails."""
@@ -217,7 +216,7 @@ def test_second_screen_own_rows_full():
     check(V, Cb)
 
 
-# From about a million rows (no codebook splits) the first screen visits the codebook in the order
+# From 2.5e10 pairs and 16384 codewords up the first screen visits the codebook in the order
 # of a key (norm, then two coordinates, each binned over a robust range of the codebook) and skips
 # pairs of tiles whose norms or coordinates are certified too far from every row of a wave; the
 # results must stay the oracle's exactly.  "constant": both key coordinates constant over the codebook
@@ -267,6 +266,67 @@ def test_pruned_first_screen(case, K):
         V = rv(n, d, 65) * np.float32(1e-30)
         Cb = rv(K, d, 66) * np.float32(1e-30)
     check(V, Cb)
+
+
+def hard_inputs(case, n, K, d, g):
+    """Rows and codewords of one of: plain, outliers (rows past the scaled fp16 range, tiny rows), ties
+    (codewords four times over), constant (no spread in the key coordinates), tiny magnitudes."""
+    if case == "ties":
+        base = rv((K + 3) // 4, d, 81)
+        Cb = np.ascontiguousarray(np.concatenate([base] * 4)[g.permutation(4 * base.shape[0])[:K]])
+        return np.concatenate([base[g.integers(0, base.shape[0], n // 2)], rv(n - n // 2, d, 82)]), Cb
+    V, Cb = rv(n, d, 83), rv(K, d, 84)
+    if case == "outliers":
+        big = g.choice(n, 300, replace=False)
+        V[big, g.integers(0, d, 300)] *= np.float32(1e6)
+        V[g.choice(n, 300, replace=False)] *= np.float32(1e-6)
+    elif case == "constant":
+        Cb[:, :2] = np.float32(0.01)
+    elif case == "tiny":
+        V, Cb = V * np.float32(1e-30), Cb * np.float32(1e-30)
+    return V, Cb
+
+
+@pytest.mark.parametrize("case,n,K,d", [
+    ("bf16", 400037, 65531, 8), ("outliers", 400037, 65531, 8), ("ties", 381600, 65536, 8), ("tiny", 400037, 65531, 8),
+    ("constant", 400037, 65531, 8), ("plain", 400037, 65531, 1)])
+def test_pruned_long_books(case, n, K, d):
+    """The pruned screen just above the pairs it starts at."""
+    say(f"pruned screen n={n} K={K} d={d} ({case})")
+    V, Cb = hard_inputs(case, n, K, d, np.random.default_rng(80))
+    if case == "bf16":
+        check(inputs.f32_to_bf16_bits(V), inputs.f32_to_bf16_bits(Cb), "bf16")
+    else:
+        check(V, Cb)
+
+
+@pytest.mark.parametrize("case,n,K,d", [
+    ("plain", 250007, 2053, 8), ("bf16", 262111, 2048, 8), ("outliers", 122077, 4096, 8), ("ties", 131071, 4100, 5),
+    ("tiny", 200003, 3001, 8), ("plain", 9001, 65536, 8), ("bf16", 8011, 65535, 3),  # 28 and more splits
+    ("constant", 183251, 16384, 8), ("ties", 190003, 16400, 8),  # the last of the split form, the first of two screens
+    ("plain", 243001, 2048, 8), ("plain", 600011, 2047, 8)])  # below the fewest pairs, the fewest codewords
+def test_split_form_at_once(case, n, K, d):
+    """Middle lengths: 32 x 32 tiles in the split form for every row, around the lines of the dispatch."""
+    say(f"split form at once n={n} K={K} d={d} ({case})")
+    V, Cb = hard_inputs(case, n, K, d, np.random.default_rng(85))
+    if case == "bf16":
+        check(inputs.f32_to_bf16_bits(V), inputs.f32_to_bf16_bits(Cb), "bf16")
+    else:
+        check(V, Cb)
+
+
+def test_beam_width_one_split_form():
+    """A width-1 beam's fp64 residual rows through the split form at once (second book), fp32 rows first."""
+    n, d = 130003, 8
+    say("width-1 beam, two books of 4096 over 130003 rows")
+    V, books = rv(n, d, 86), [rv(4096, d, 87), rv(4096, d, 88, 0.01)]
+    codes = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in books]
+    err = torch.empty(n, dtype=torch.float32, device="cuda")
+    C.crvq_assign_residual_beam(VecSet.of_vectors(dev(V)), [dev(b) for b in books], 1, codes, err)
+    torch.cuda.synchronize()
+    exp_codes, exp_err = oracle.beam(V, books, 1)
+    np.testing.assert_array_equal(np.stack([c.cpu().numpy() for c in codes]), exp_codes)
+    np.testing.assert_array_equal(err.cpu().numpy(), exp_err.astype(np.float32))
 
 
 def test_rescue_of_most_rows():
