@@ -606,6 +606,7 @@ constexpr int64_t kRescuePartMinK = 8192;  // codebooks from which the top-1 res
 // at any length (x 2 M 275 / 321).
 constexpr int64_t kS32MinK = 2048;
 constexpr int64_t kS32MinPairs = 500000000;      // rows x codewords
+constexpr int64_t kS32ShortMaxRows = 3600000;    // 36 bytes each: within 128 MiB
 constexpr int64_t kS32DirectPairs = 3000000000;  // unpruned: below, every row takes the split form at once
 constexpr int64_t kS32SharedRowsMaxN = int64_t{1} << 23;  // second screen: shared rows below this n
 constexpr int kS32TileHalves = 768;  // packed fp16 per tile: c1, c2, N terms, 32 x 8 each
@@ -2884,7 +2885,10 @@ ScreenPlan plan_screen(int64_t n_rows, int d, int64_t K, int top) {
   p.grid_x = cdiv(n_rows, 64 * p.cb);
   int64_t splits = 1;
   // Long top-1 searches: 32 x 32 split-fp16 tiles (two MFMAs per 1024 values instead of four).
-  const bool s32 = p.split && CRVQ_S32_SCREEN && p.nb == 1 && K >= kS32MinK && n_rows * K >= kS32MinPairs;
+  // Their scratch is 36 bytes a row against 28: under 4096 codewords, rows past kS32ShortMaxRows keep
+  // the form that fits the fixed scratch of crvq_assign_noalloc.
+  const bool s32 = p.split && CRVQ_S32_SCREEN && p.nb == 1 && K >= kS32MinK && n_rows * K >= kS32MinPairs &&
+                   (K >= 4096 || n_rows <= kS32ShortMaxRows);
   const int64_t want_blocks = 2048;
   p.prune = 0;
   if (s32) {

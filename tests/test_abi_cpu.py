@@ -292,6 +292,20 @@ def test_refinement_validation(L):
     assert L.crvq_hessian_inverse_diagonal(None, 0, 0, dbl(0.01), None, None, None, 0, None) == 0     # N = 0
 
 
+@pytest.mark.parametrize("n,d,K", [(4_700_000, 8, 256), (4_700_000, 8, 1024), (4_700_000, 8, 2048), (4_700_000, 5, 4095),
+                                   (3_600_000, 8, 2048), (3_600_000, 8, 4095), (3_600_001, 8, 3000), (2_500_000, 8, 65536)])
+def test_assign_scratch_fits_noalloc(L, n, d, K):
+    """Searches the fixed scratch of crvq_assign_noalloc holds, whichever screen they take."""
+    assert 0 < L.crvq_assign_workspace_size(n, d, K) <= 128 << 20
+
+
+@pytest.mark.parametrize("K", [257, 512, 4096, 65536])
+def test_kmeans_workspace_grows_with_vectors(L, K):
+    """The chunk length steps up with the vectors; a larger set's workspace still holds a smaller set's."""
+    sizes = [L.crvq_kmeans_workspace_size(n, 8, K) for n in range(1, 3_000_000, 9973)]
+    assert sizes == sorted(sizes)
+
+
 def test_workspace_size_dispatcher(L):
     """crvq_workspace_size(op, ...) returns what the per-call sizing function returns for the same
     shape, for every op, and 0 for an unknown op or a rejected shape."""
