@@ -577,13 +577,27 @@ int64_t wave_blocks(int64_t n) {
 
 // ---- large codebooks (256 < K <= 65536) ----------------------------------------------------------
 // One stable radix pass groups the vectors by the high byte of their code (256 buckets of 256 codes).
-// Every bucket is then cut into chunks of kChunk vectors; a block takes one chunk and runs the
+// Every bucket is then cut into chunks of chunk_len(n, K) vectors; a block takes one chunk and runs the
 // small-codebook scheme on the low byte, gathering each member vector with 16-byte loads.  The
 // chunk partials of each code are folded in chunk order.
-#ifndef CRVQ_KM_CHUNK
-#define CRVQ_KM_CHUNK 4096
-#endif
-constexpr int kChunk = CRVQ_KM_CHUNK;
+// Members per chunk.  A chunk is a workgroup's serial work, and every chunk of a bucket adds a partial that
+// bucket_final folds: short chunks where few would leave the chip idle, unless a bucket gets many.
+// Measured with chunks of 4096 / 2048 / 1024, us: K = 4096 x 80,000 vectors 72 / 58 / 52, x 386,625 83 / 70 /
+// 69, x 800,000 90 / 82 / 94, x 1.5 M 102 / 103 / 123; K = 512 x 80,000 74 / 64 / 63, x 386,625 92 / 94 / 114;
+// K = 65536 x 800,000 85 / 76 / 79, x 2.1 M 107 / 115 / 118; d = 16, K = 4096 x 200,000 198 / 131 / 96.
+constexpr int64_t kChunk1Max = 400000, kChunk2Max = 1500000;
+int chunk_len(int64_t n, int64_t K) {
+  const int64_t per_bucket = n / cdiv(K, 256);
+  if (n <= kChunk1Max && per_bucket <= 64000) return 1024;
+  return n <= kChunk2Max && per_bucket <= 160000 ? 2048 : 4096;
+}
+
+// Chunks of n vectors, whatever K (never fewer for more vectors, so that a larger set's workspace does).
+int64_t most_chunks(int64_t n) {
+  const int64_t c1 = cdiv(n < kChunk1Max ? n : kChunk1Max, 1024), c2 = cdiv(n < kChunk2Max ? n : kChunk2Max, 2048);
+  const int64_t c4 = cdiv(n, 4096), c = c1 > c2 ? c1 : c2;
+  return (c > c4 ? c : c4) + 256;  // every bucket adds at most one partial chunk
+}
 
 // bounds of the 256 high-byte buckets and of their chunk ranges (one block)
 // Chunks are also enumerated level by level (chunk j of every bucket that has one, buckets in
@@ -593,14 +607,14 @@ constexpr int kChunk = CRVQ_KM_CHUNK;
 // every bucket at once.
 __global__ __launch_bounds__(256) void bucket_bounds(const int* __restrict__ offs, int64_t n_tiles,
                                                      const int* __restrict__ n_valid, int* __restrict__ bstart,
-                                                     int* __restrict__ cstart, int* __restrict__ lstart) {
+                                                     int* __restrict__ cstart, int* __restrict__ lstart, int chunk_n) {
   __shared__ int sh[256];
   __shared__ int nch[256];
   __shared__ int maxc;
   const int b = threadIdx.x;
   const int s = offs[static_cast<int64_t>(b) * n_tiles];
   const int e = (b < 255) ? offs[static_cast<int64_t>(b + 1) * n_tiles] : *n_valid;
-  const int chunks = (e - s + kChunk - 1) / kChunk;
+  const int chunks = (e - s + chunk_n - 1) / chunk_n;
   int total;
   const int ex = block_exclusive_scan(chunks, sh, total);
   bstart[b] = s;
@@ -637,7 +651,7 @@ __global__ __launch_bounds__(256) void bucket_bounds(const int* __restrict__ off
 __global__ __launch_bounds__(256) void bucket_partial(RowSrc src, const int* __restrict__ keys,
                                                       const int* __restrict__ vals, const int* __restrict__ bstart,
                                                       const int* __restrict__ cstart, double* __restrict__ part,
-                                                      int* __restrict__ pcount) {
+                                                      int* __restrict__ pcount, int chunk_n) {
   __shared__ RoundLds L;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int blk = blockIdx.x;
@@ -651,8 +665,8 @@ __global__ __launch_bounds__(256) void bucket_partial(RowSrc src, const int* __r
       hi = mid;
   }
   const int b = lo;
-  const int64_t b0 = bstart[b] + static_cast<int64_t>(blk - cstart[b]) * kChunk;
-  const int64_t b1 = (b0 + kChunk < bstart[b + 1]) ? b0 + kChunk : bstart[b + 1];
+  const int64_t b0 = bstart[b] + static_cast<int64_t>(blk - cstart[b]) * chunk_n;
+  const int64_t b1 = (b0 + chunk_n < bstart[b + 1]) ? b0 + chunk_n : bstart[b + 1];
   const int d = src.d;
   double acc[16];
 #pragma unroll
@@ -698,7 +712,7 @@ __global__ __launch_bounds__(256) void bucket_partial(RowSrc src, const int* __r
 __global__ __launch_bounds__(256) void bucket_partial8(RowSrc src, const int* __restrict__ keys,
                                                        const int* __restrict__ vals, const int* __restrict__ bstart,
                                                        const int* __restrict__ cstart, const int* __restrict__ lstart,
-                                                       double* __restrict__ part, int* __restrict__ pcount) {
+                                                       double* __restrict__ part, int* __restrict__ pcount, int chunk_n) {
   __shared__ RoundLds L;
   __shared__ float4 stage[kRound][2];
   __shared__ int s_bucket;
@@ -726,8 +740,8 @@ __global__ __launch_bounds__(256) void bucket_partial8(RowSrc src, const int* __
   }
   const int b = s_bucket;
   const int blk = cstart[b] + j;  // partials stay in bucket-major order
-  const int64_t b0 = bstart[b] + static_cast<int64_t>(j) * kChunk;
-  const int64_t b1 = (b0 + kChunk < bstart[b + 1]) ? b0 + kChunk : bstart[b + 1];
+  const int64_t b0 = bstart[b] + static_cast<int64_t>(j) * chunk_n;
+  const int64_t b1 = (b0 + chunk_n < bstart[b + 1]) ? b0 + chunk_n : bstart[b + 1];
   const int d = src.d;
   const bool packed = src.ld == src.vpr * d;
   double acc[8];
@@ -862,7 +876,7 @@ KmWs carve(WsCursor& ws, int64_t n, int64_t K) {
   w.n_valid = ws.take<int>(1);
   w.bstart = ws.take<int>(257);
   w.cstart = ws.take<int>(258);  // [256] = chunks, [257] = levels
-  w.max_chunks = cdiv(n, kChunk) + 256;  // every bucket adds at most one partial chunk
+  w.max_chunks = most_chunks(n);
   w.lstart = ws.take<int>(static_cast<size_t>(w.max_chunks + 1));
   w.part = ws.take<double>(static_cast<size_t>(w.max_chunks) * 256 * 16);
   w.pcount = ws.take<int>(static_cast<size_t>(w.max_chunks) * 256);
@@ -913,9 +927,9 @@ hipError_t launch_code_sums_large(const RowSrc& src, const int32_t* codes, int64
   hipLaunchKernelGGL(radix_scatter, dim3(static_cast<unsigned>(n_tiles)), dim3(256), 0, stream, codes, nullptr, nullptr,
                      n, K, 0, 8, n_tiles, w.offs, w.keys, w.vals);
   hipLaunchKernelGGL(bucket_bounds, dim3(1), dim3(256), 0, stream, w.offs, n_tiles, w.n_valid, w.bstart, w.cstart,
-                     w.lstart);
+                     w.lstart, chunk_len(n, K));
   hipLaunchKernelGGL(bucket_partial, dim3(static_cast<unsigned>(w.max_chunks)), dim3(256), 0, stream, src, w.keys,
-                     w.vals, w.bstart, w.cstart, w.part, w.pcount);
+                     w.vals, w.bstart, w.cstart, w.part, w.pcount, chunk_len(n, K));
   hipLaunchKernelGGL(bucket_final_sums, dim3(static_cast<unsigned>(cdiv(K * src.d, 256))), dim3(256), 0, stream,
                      w.part, w.pcount, w.cstart, K, src.d, sums, counts);
   return hipGetLastError();
@@ -963,13 +977,13 @@ hipError_t launch_kmeans_update(const RowSrc& src, const int32_t* codes, int64_t
   hipLaunchKernelGGL(radix_scatter, dim3(static_cast<unsigned>(n_tiles)), dim3(256), 0, stream, codes, nullptr, nullptr,
                      n, K, 0, 8, n_tiles, w.offs, w.keys, w.vals);
   hipLaunchKernelGGL(bucket_bounds, dim3(1), dim3(256), 0, stream, w.offs, n_tiles, w.n_valid, w.bstart, w.cstart,
-                     w.lstart);
+                     w.lstart, chunk_len(n, K));
   if (src.d <= 8 && src.type != ET_F64)
     hipLaunchKernelGGL(bucket_partial8, dim3(static_cast<unsigned>(w.max_chunks)), dim3(256), 0, stream, src, w.keys,
-                       w.vals, w.bstart, w.cstart, w.lstart, w.part, w.pcount);
+                       w.vals, w.bstart, w.cstart, w.lstart, w.part, w.pcount, chunk_len(n, K));
   else
     hipLaunchKernelGGL(bucket_partial, dim3(static_cast<unsigned>(w.max_chunks)), dim3(256), 0, stream, src, w.keys,
-                       w.vals, w.bstart, w.cstart, w.part, w.pcount);
+                       w.vals, w.bstart, w.cstart, w.part, w.pcount, chunk_len(n, K));
   hipLaunchKernelGGL(bucket_final, dim3(static_cast<unsigned>(cdiv(K * src.d, 256))), dim3(256), 0, stream, w.part,
                      w.pcount, w.cstart, K, src.d, C, c_type, counts);
   return hipGetLastError();
