@@ -562,3 +562,25 @@ def test_kmeans_update_few_and_wide(n, K, d, dtype, pad):
     np.testing.assert_array_equal(counts.cpu().numpy(), cnt)
     rel_close(oracle.widen(to_host_bits(Ct), dtype), oracle.widen(Cexp, dtype), 2.0 ** -23 if dtype == "f32" else 2.0 ** -7,
               "centroids", axis_vec=True)
+
+
+@pytest.mark.parametrize("n,K,d", [(1, 257, 8), (128255, 512, 8), (128257, 512, 16), (320257, 512, 8), (400000, 4096, 8),
+                                   (400001, 4096, 12), (1500000, 65536, 8), (1500001, 65536, 8)])
+def test_kmeans_update_chunk_lengths(n, K, d):
+    """Larger codebooks on both sides of each line between chunk lengths, a third of the members in one
+    bucket; against fp64 means (the sum's order moves the fp32 result by its last place at most)."""
+    say(f"kmeans update chunks n={n} K={K} d={d}")
+    g = np.random.default_rng(n)
+    V = rv(n, d, 90)
+    q = g.integers(0, K, n).astype(np.int32)
+    q[: n // 3] %= 256
+    Cb = rv(K, d, 91)
+    Ct, counts = dev(Cb), torch.empty(K, dtype=torch.int32, device="cuda")
+    C.crvq_kmeans_update(VecSet.of_vectors(dev(V)), dev(q), Ct, counts)
+    torch.cuda.synchronize()
+    cnt = np.bincount(q, minlength=K)
+    exp = np.stack([np.bincount(q, weights=V[:, t].astype(np.float64), minlength=K) for t in range(d)], 1)
+    exp = np.where(cnt[:, None] > 0, exp / np.maximum(cnt, 1)[:, None], Cb)
+    np.testing.assert_array_equal(counts.cpu().numpy(), cnt)
+    # half a last place from the rounding, and n additions of |v| < 0.2 in fp64
+    np.testing.assert_allclose(Ct.cpu().numpy(), exp, rtol=2.0 ** -23, atol=1e-15)
