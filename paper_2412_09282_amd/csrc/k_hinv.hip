@@ -83,8 +83,10 @@ __global__ __launch_bounds__(256) void hinv_init_kernel(const double* __restrict
 }
 
 // 1 / sqrt(x) and 1 / x for x > 0: the hardware estimates (good to about 2^-22) refined by two Newton
-// steps, each of which squares the relative error; a few ulps from the rounded quotient.  Not positive or
-// not finite x gives NaN, 0 or inf, which the caller's pivot check has already flagged.
+// steps, each of which squares the relative error; a few ulps from the rounded quotient.  rcp_f64 needs x and
+// 1 / x to be normal numbers, kPivotMin <= x <= kPivotMax; rsqrt_f64 gives NaN, 0 or inf for x that is not positive
+// or not finite.
+constexpr double kPivotMin = 0x1p-1020, kPivotMax = 0x1p1020;
 __device__ __forceinline__ double rsqrt_f64(double x) {
   double y = __builtin_amdgcn_rsq(x);
 #pragma unroll
@@ -120,10 +122,9 @@ __device__ __forceinline__ void panel_rest(double (&x)[16], double (&z)[16], dou
   }
 }
 template <int C>
-__device__ __forceinline__ void panel_column(double (&x)[16], double (&z)[16], double before, bool& bad) {
+__device__ __forceinline__ void panel_column(double (&x)[16], double (&z)[16], double before) {
   if constexpr (C < 16) {
     const double d = bcast16<C>(z[C]);
-    bad = bad || !(d > 0.0 && d < __builtin_inf());
     const double inv = rcp_f64(d);
     // column C - 1 leaves the columns after C while the reciprocal is formed
     if constexpr (C > 0) panel_rest<C - 1, C + 1>(x, z, before);
@@ -133,7 +134,7 @@ __device__ __forceinline__ void panel_column(double (&x)[16], double (&z)[16], d
       z[C + 1] = __builtin_fma(-z[C], wj, z[C + 1]);
       x[C + 1] = __builtin_fma(-x[C], wj, x[C + 1]);
     }
-    panel_column<C + 1>(x, z, w, bad);
+    panel_column<C + 1>(x, z, w);
   }
 }
 template <int C>
@@ -143,19 +144,37 @@ __device__ __forceinline__ void panel_scale(double (&x)[16], double r) {
     panel_scale<C + 1>(x, r);
   }
 }
+// The same sweep with every column divided by the root of its pivot at once, without reciprocals.
+template <int C>
+__device__ __forceinline__ void panel_column_any(double (&x)[16], double (&z)[16]) {
+  if constexpr (C < 16) {
+    const double r = rsqrt_f64(bcast16<C>(z[C]));
+    x[C] = x[C] * r;
+    z[C] = z[C] * r;
+    panel_rest<C, C + 1>(x, z, z[C]);
+    panel_column_any<C + 1>(x, z);
+  }
+}
 // 16 columns of a lower triangular factorization: x is a row of them (or, started as a unit vector, a
 // column of the diagonal block's inverse factor: forward substitution on the identity is the same
 // sweep); z is row lane % 16 of their diagonal block, so that every 16 lanes hold the whole block and a
 // pivot row's element reaches the others by one DPP move.  The sweep keeps the columns unscaled,
 // x_j -= x_c (z_jc / d_c), so that from one pivot to the next stand only the reciprocal, a product, a
 // fused multiply-add and two moves; the columns are divided by sqrt(d_c) at the end, lane c of 16
-// forming the root of d_c.
-__device__ __forceinline__ void panel16(double (&x)[16], double (&z)[16], int lane, bool& bad) {
-  panel_column<0>(x, z, 0.0, bad);
+// forming the root of d_c.  ok becomes false when d_c is not a pivot that rcp_f64 takes.  ANY: any positive pivots
+// (chain of the root and its reciprocal per column); ok becomes false when one is not positive and finite.
+template <bool ANY>
+__device__ __forceinline__ void panel16(double (&x)[16], double (&z)[16], int lane, bool& ok) {
+  if constexpr (ANY)
+    panel_column_any<0>(x, z);
+  else
+    panel_column<0>(x, z, 0.0);
+  // ANY: the pivot times the estimate of its root's reciprocal, NaN unless 0 < pivot < inf
   double d = z[0];
 #pragma unroll
   for (int c = 1; c < 16; ++c) d = (lane & 15) == c ? z[c] : d;
-  panel_scale<0>(x, rsqrt_f64(d));
+  ok = ok && (ANY ? d > 0.0 && d < __builtin_inf() : d >= kPivotMin && d <= kPivotMax);
+  if constexpr (!ANY) panel_scale<0>(x, rsqrt_f64(d));
 }
 
 // LDS of the diagonal block's factorization: L on and below the diagonal of Ab; the inverse's 16 x 16
@@ -163,6 +182,7 @@ __device__ __forceinline__ void panel16(double (&x)[16], double (&z)[16], int la
 struct DiagLds {
   double Ab[kHb][kHr];
   double Td[4][16][18];
+  int ok;  // every pivot was one
 };
 
 // acc += P Q for 16 x 16 tiles in LDS (row-major, strides sp and sq), two chains of products
@@ -206,10 +226,12 @@ __device__ __forceinline__ void inverse_block(DiagLds& S, int i, int j, int t, i
 // Four panels of 16 columns: wave 0 holds the panel's rows down to 63 in registers, wave 1 forms the
 // inverse of the panel's diagonal block; then the rank-16 update of the rest on the matrix cores.
 // T_ij = -T_ii sum_k L_ik T_kj: waves 2 and 3 form the blocks whose operands are there beside the
-// panels, so that only the last row's product with T_33 is left.  Bound by the chain of 64 pivots.
-__device__ __forceinline__ void factor_diag(DiagLds& S, double* __restrict__ out, int64_t ld, int* __restrict__ flag) {
+// panels, so that only the last row's product with T_33 is left.  Bound by the chain of 64 pivots.  Returns
+// whether every pivot was in the range of panel16<ANY>; if not, the results are nothing.
+template <bool ANY>
+__device__ __forceinline__ bool factor_sweep(DiagLds& S, double* __restrict__ out, int64_t ld) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
-  bool bad = false;
+  bool ok = true;
   for (int b = 0; b < 4; ++b) {
     const int c0 = 16 * b;
     if (wave < 2) {
@@ -223,7 +245,7 @@ __device__ __forceinline__ void factor_diag(DiagLds& S, double* __restrict__ out
 #pragma unroll
         for (int j = 0; j < 16; ++j) x[j] = j == li ? 1.0 : 0.0;
       }
-      panel16(x, z, lane, bad);
+      panel16<ANY>(x, z, lane, ok);
       if (wave == 0) {
         // wave 1 may still be reading the diagonal block's rows; the rows below are wave 0's alone
         if (lane >= c0 + 16) {
@@ -266,7 +288,10 @@ __device__ __forceinline__ void factor_diag(DiagLds& S, double* __restrict__ out
       }
     if (b < 3) __syncthreads();
   }
-  if (tid == 0 && bad) flag[0] = 1;
+  if (wave == 0) {
+    const bool all = __ballot(!ok) == 0;
+    if (lane == 0) S.ok = all;
+  }
   if (wave < 3) inverse_block(S, 3, wave, wave, li, lk);
   __syncthreads();
 #pragma unroll
@@ -275,6 +300,17 @@ __device__ __forceinline__ void factor_diag(DiagLds& S, double* __restrict__ out
     const double* v = rb == cb ? &S.Td[rb][r & 15][c & 15] : &S.Ab[16 * cb + (r & 15)][16 * rb + (c & 15)];
     out[r * ld + c] = rb >= cb ? *v : 0.0;
   }
+  return S.ok != 0;
+}
+// The same with the pivots outside rcp_f64's range (a block in memory that holds magnitudes past 1e+-307: hardly
+// ever) in a second sweep, from the block's copy in memory.
+__device__ __forceinline__ void factor_diag(DiagLds& S, const double* __restrict__ block, double* __restrict__ out,
+                                            int64_t ld, int* __restrict__ flag) {
+  if (factor_sweep<false>(S, out, ld)) return;
+  __syncthreads();
+  for (int e = threadIdx.x; e < kHb * kHb; e += 256) S.Ab[e >> 6][e & 63] = block[(e >> 6) * ld + (e & 63)];
+  __syncthreads();
+  if (!factor_sweep<true>(S, out, ld) && threadIdx.x == 0) flag[0] = 1;
 }
 
 // acc = sum_k a(i, k) b(k, j) over K (a multiple of 16) for a 64 x (32 MB) tile, 32 x (16 MB) per wave.
@@ -365,7 +401,7 @@ __global__ __launch_bounds__(256) void hinv_first_kernel(const double* __restric
   __shared__ DiagLds S;
   for (int e = threadIdx.x; e < kHb * kHb; e += 256) S.Ab[e >> 6][e & 63] = A[(e >> 6) * Np + (e & 63)];
   __syncthreads();
-  factor_diag(S, T, Np, flag);
+  factor_diag(S, A, T, Np, flag);
 }
 
 // The panel of block column k in place, L_ik = A_ik D_k^T: 16 rows per workgroup (so that the few block
@@ -410,16 +446,19 @@ __global__ __launch_bounds__(256) void hinv_update_kernel(double* __restrict__ A
   int64_t a, b;
   tri_index(blockIdx.x, a, b);
   const int64_t kb = k * kHb, ib = (k + 1 + a) * kHb, jb = (k + 1 + b) * kHb;
-  double* C = A + ib * Np + jb;
+  double* C = A + ib * Np + jb;  // (jb = ib for workgroup 0)
   double old[16];
   UpdateTile t;
   t.each([&](int i, int j, double, int n) { old[n] = C[i * Np + j]; });
   t.run(S.tile, A + ib * Np + kb, Np, A + jb * Np + kb, Np, kHb);
   if (blockIdx.x == 0) {
     __syncthreads();  // the operand buffers are the diagonal block's memory
-    t.each([&](int i, int j, double v, int n) { S.diag.Ab[i][j] = old[n] - v; });
+    t.each([&](int i, int j, double v, int n) {
+      S.diag.Ab[i][j] = old[n] - v;
+      C[i * Np + j] = old[n] - v;
+    });
     __syncthreads();
-    factor_diag(S.diag, T + ib * Np + ib, Np, flag);
+    factor_diag(S.diag, C, T + ib * Np + ib, Np, flag);
     return;
   }
   t.each([&](int i, int j, double v, int n) { C[i * Np + j] = old[n] - v; });

@@ -140,3 +140,19 @@ def test_hinv_block_counts(N):
     and without one."""
     rng = np.random.default_rng([2413, N])
     _check(gram(_calib(rng, N // 2 + 3, N)), 0.01, f"hinv blocks N={N}")
+
+
+@pytest.mark.parametrize("lo,hi", [(-1030, -1000), (-1030, 1019), (1015, 1022)])
+@pytest.mark.parametrize("N", [17, 130])
+def test_hinv_extreme_pivots(N, lo, hi):
+    """Pivots whose reciprocal is subnormal or beyond fp64, subnormal pivots, and both among ordinary ones: each
+    [A^-1]_jj of a diagonal matrix is 1 / h_j (within a few roundings; beyond fp64: inf)."""
+    rng = np.random.default_rng([2414, N, 2000 + hi])
+    e = np.floor(np.linspace(lo, hi - np.log2(N) - 1, N)).astype(int)  # (the trace stays in range)
+    h = np.ldexp(rng.uniform(1.0, 1.9, N), rng.permutation(e))
+    say(f"hinv extreme pivots N={N} 2^{lo}..2^{hi}")
+    got, _ = _gpu(np.diag(h), 0.0)
+    with np.errstate(over="ignore"):
+        exp = 1.0 / h
+    # the root and its reciprocal, the division's own rounding and a square; two last places of a subnormal result
+    np.testing.assert_allclose(got, exp, rtol=8 * EPS, atol=2.0 ** -1073)
