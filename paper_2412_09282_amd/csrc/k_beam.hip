@@ -4,13 +4,17 @@
 // A vector's candidates are its n_par parents' residuals against all K codewords; the n_next smallest
 // keys (distance in fp64, parent rank, codeword) survive.  A wave takes 16 rows (16 / PP vectors of PP
 // parent slots, PP a power of two) and keeps all their screen values in registers (SplitOps, 16 tiles of
-// 16 codewords, 64 values per lane).  With
-//   lower = s + ||x||^2 - delta <= distance <= s + ||x||^2 + delta = upper,
-// delta the row's bound of the screen's error for any codeword of the book, the n_next-th smallest upper
-// bound U of a vector's 32 (64) groups of candidates is no less than its n_next-th smallest distance, so every survivor
-// is among the candidates with lower <= U: about a dozen of 2048, which alone are scored exactly and
-// ranked by their keys.  A vector with more than kCap of them (or a row the screen could not bound, as
-// with a NaN) is searched exactly by its wave.  Bound by VALU issue (about 1040 instructions per 16 rows,
+// 16 codewords, 64 values per lane).  The screen's error for a codeword c is at most
+//   a (||c|| + ||x||)^2 + b ||c|| ||x|| <= e (||c||^2 + ||x||^2),  e = 2 a + b / 2
+// (a its roundings, b the split remainders).  The share of the codeword's own norm goes into the norm the
+// screen starts from, ||c||^2 (1 - e), so that one long codeword does not widen the others' bounds: the
+// screen value A gives
+//   lower = A + (1 - e) ||x||^2 <= D <= (A + (1 + 5 e) ||x||^2) / (1 - 4 e) = upper,
+// the second from D <= A + (1 + e) ||x||^2 + 2 e ||c||^2 and ||c||^2 <= 2 ||x||^2 + 2 D.  The n_next-th smallest
+// upper bound U of a vector's 32 (64) groups of candidates is no less than its n_next-th smallest distance, so
+// every survivor is among the candidates with lower <= U: about a dozen of 2048, which alone are scored
+// exactly and ranked by their keys.  A vector with more than kCap of them (or a row the screen could not
+// bound, as with a NaN) is searched exactly by its wave.  Bound by VALU issue (about 1040 instructions per 16 rows,
 // 73 % of the cycles).  The width-8 beam over three books of 256 for 286,208 vectors takes 0.72 ms; with
 // per-parent top-8 lists, their re-scored tiles (40 codewords per parent row) and a merge through memory
 // it took 2.27 ms.  Residuals are formed from the vector and the parent's
@@ -25,6 +29,12 @@ namespace {
 struct BeamBooks {
   const void* C[kMaxBooks];
   int type[kMaxBooks];
+};
+
+// Factors of the bounds above: the codewords' norms, ||x||^2 and the whole of the upper bound, ||x||^2 of the
+// lower one.
+struct BeamBound {
+  float cn, up, up_d, low;
 };
 
 // An aligned pair of fp32 or bf16 elements as raw words: fp32 both of them, bf16 the same word twice.
@@ -42,6 +52,8 @@ struct RawPair {
     return static_cast<double>(__uint_as_float(bf16 ? b & 0xffff0000u : b));
   }
 };
+constexpr float kBmFar = 1.0e37f;   // ||x||^2 and distances the screen may handle
+constexpr float kBmTiny = 2.0e-35f;  // products below the operands' normal range
 constexpr int kBmAhead = 3;  // earlier books whose codewords are loaded one pass ahead
 
 constexpr int kBmWaves = 4;
@@ -156,7 +168,7 @@ __device__ __forceinline__ void vector_list(float (&u)[kBmGroups<PP>], float (&l
 template <int PP, bool PAIRS>
 __global__ __launch_bounds__(64 * kBmWaves, 3) void beam_small_kernel(RowSrc src, int64_t n, int n_par, int n_next,
                                                                   int step, int n_books, BeamBooks books, int K,
-                                                                  float split_coef, const int* __restrict__ tup_in,
+                                                                  BeamBound eb, const int* __restrict__ tup_in,
                                                                   int* __restrict__ tup_out, double* __restrict__ res_out,
                                                                   int last, CodePtrs outs, int64_t vpr,
                                                                   float* __restrict__ err_out) {
@@ -169,7 +181,6 @@ __global__ __launch_bounds__(64 * kBmWaves, 3) void beam_small_kernel(RowSrc src
   __shared__ uint16_t apack[256 * 16];
   __shared__ float cn[256];
   __shared__ float cf[256][8];
-  __shared__ float rpart[kBmWaves];
   __shared__ double xr_s[kBmWaves][16][10];
   __shared__ double candD_s[kBmWaves][kBmCand];
   __shared__ int candK_s[kBmWaves][kBmCand];
@@ -194,18 +205,11 @@ __global__ __launch_bounds__(64 * kBmWaves, 3) void beam_small_kernel(RowSrc src
       hi[t] = h;
       lo[t] = l;
     }
-    cn[k] = k < K ? nrm : __builtin_inff();
+    cn[k] = k < K ? nrm * eb.cn : __builtin_inff();
     reinterpret_cast<u16x8*>(apack)[2 * k] = hi;
     reinterpret_cast<u16x8*>(apack)[2 * k + 1] = lo;
-    float m = k < K ? nrm : 0.0f;
-#pragma unroll
-    for (int w = 1; w < 64; w <<= 1) m = fmaxf(m, __shfl_xor(m, w));
-    if (lane == 0) rpart[wave] = m;
   }
   __syncthreads();
-  // R >= ||c|| for every codeword: the fp32 norm is within 2^-20, the hardware root within one ulp
-  const float R = __builtin_amdgcn_sqrtf(fmaxf(fmaxf(rpart[0], rpart[1]), fmaxf(rpart[2], rpart[3]))) * (1.0f + 0x1p-18f) +
-                  1e-18f;
   const int tiles = (K + 15) / 16;
   double(*xr)[10] = xr_s[wave];
   double* candD = candD_s[wave];
@@ -307,26 +311,25 @@ __global__ __launch_bounds__(64 * kBmWaves, 3) void beam_small_kernel(RowSrc src
     }
 #pragma unroll
     for (int T = 0; T < 16; ++T) tm[T] = fminf(fminf(acc[T][0], acc[T][1]), fminf(acc[T][2], acc[T][3]));
-    // the screen's error for any codeword of norm <= R (the terms of ScreenBound), the fp32 roundings of
-    // the bounds themselves within 16 2^-24 (R + ||x||)^2
     const float xn2f = static_cast<float>(xn2);
-    const float rx = __builtin_amdgcn_sqrtf(xn2f) * (1.0f + 0x1p-20f) + 1e-18f;
-    const float delta = (112.0f * 0x1p-24f * (R + rx) * (R + rx) + split_coef * rx * R) * (1.0f + 0x1p-10f) +
-                        0x1p-118f * (R + rx + 1.0f) + 1e-35f;
-    float u[S], best[8];
+    // past this a norm or a sum of the screen may leave fp32's range: the vector is searched exactly
+    const bool far = row_ok && !(xn2f < kBmFar);
+    const float xu = xn2f + (eb.up * xn2f + kBmTiny), xl = (eb.low * xn2f + kBmTiny) - xn2f;
+    float u[S], best[8];  // the upper bounds but for their common factor
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       float m = __builtin_inff();
 #pragma unroll
       for (int T = s * (16 / S); T < (s + 1) * (16 / S); ++T) m = fminf(m, tm[T]);
-      u[s] = row_ok ? m + xn2f + delta : __builtin_inff();
+      u[s] = row_ok ? m + xu : __builtin_inff();
     }
     vector_list<PP>(u, best);
     float U = best[0];
 #pragma unroll
     for (int j = 1; j < 8; ++j) U = j < n_next ? best[j] : U;
+    U *= eb.up_d;
     // lower <= U; a padding codeword (+inf) never is
-    const float thr = row_ok ? fminf(U - xn2f + delta, 3.0e38f) : -3.0e38f;
+    const float thr = row_ok ? fminf(U + xl, 3.0e38f) : -3.0e38f;
     // each lane's hits as bits (value 0 of a half in the highest), then one list entry per lane and round
     int cnt = 0;
 #pragma unroll
@@ -345,7 +348,8 @@ __global__ __launch_bounds__(64 * kBmWaves, 3) void beam_small_kernel(RowSrc src
       }
     }
     wave_sync();
-    const bool fits = cnt <= kCap && cnt >= n_next;
+    const bool sure = U < kBmFar && (__ballot(far) & vmask) == 0;  // (U is +inf where a small book fills few groups)
+    const bool fits = cnt <= kCap && cnt >= n_next && (sure || cnt == n_par * K);
     // a child: its codes, residual and error
     auto child = [&](int64_t iv, int vv, int rank, int pp, int k, double D, bool none) {
       if (last) {
@@ -449,9 +453,11 @@ hipError_t launch_beam_small(const RowSrc& src0, int n_par, int n_next, int step
     b.C[t] = C[t];
     b.type[t] = types[t];
   }
-  // the split remainder of each operand that is not bf16 already (screen_bound)
+  // a = 112 roundings of the screen (screen_bound's 96 and those of the scaled norms), b the split remainder of
+  // each operand that is not bf16 already
   const int inexact = (step > 0 || src0.type != ET_BF16 ? 1 : 0) + (types[step] != ET_BF16 ? 1 : 0);
-  const float coef = 0x1p-15f * static_cast<float>(inexact) * (1.0f + 0x1p-6f);
+  const float ec = 2.0f * 112.0f * 0x1p-24f + 0.5f * 0x1p-15f * static_cast<float>(inexact) * (1.0f + 0x1p-6f);
+  const BeamBound eb = {1.0f - ec, 5.0f * ec + 0x1p-20f, 1.0f + 4.25f * ec + 0x1p-20f, ec + 0x1p-20f};
   const int pp = n_par <= 1 ? 1 : n_par <= 2 ? 2 : n_par <= 4 ? 4 : 8;
   const int64_t passes = cdiv(src0.n, 16 / pp), blocks = cdiv(passes, kBmWaves);
   const dim3 grid(static_cast<unsigned>(blocks < 768 ? blocks : 768));
@@ -461,7 +467,7 @@ hipError_t launch_beam_small(const RowSrc& src0, int n_par, int n_next, int step
   for (int t = 0; t < step; ++t) pairs = pairs && aligned(C[t], types[t]);
 #define CRVQ_BEAM2(PPV, PR)                                                                                          \
   hipLaunchKernelGGL((beam_small_kernel<PPV, PR>), grid, dim3(64 * kBmWaves), 0, stream, src0, src0.n, n_par, n_next, step, \
-                     n_books, b, static_cast<int>(K), coef, tup_in, tup_out, res_out, last ? 1 : 0, outs, vpr, err_out)
+                     n_books, b, static_cast<int>(K), eb, tup_in, tup_out, res_out, last ? 1 : 0, outs, vpr, err_out)
 #define CRVQ_BEAM(PPV)     \
   if (pairs)               \
     CRVQ_BEAM2(PPV, true); \

@@ -584,3 +584,65 @@ def test_kmeans_update_chunk_lengths(n, K, d):
     np.testing.assert_array_equal(counts.cpu().numpy(), cnt)
     # half a last place from the rounding, and n additions of |v| < 0.2 in fp64
     np.testing.assert_allclose(Ct.cpu().numpy(), exp, rtol=2.0 ** -23, atol=1e-15)
+
+
+@pytest.mark.parametrize("beam", [1, 2, 4, 8])
+@pytest.mark.parametrize("case", ["long_codewords", "long_vectors", "norms_past_fp32"])
+def test_beam_small_books_norm_spread(beam, case):
+    """Books and vectors of very different norms: a few codewords 300 times as long as the rest; long vectors
+    among them; norms whose squares leave fp32's range, near and far from the vectors."""
+    say(f"beam norm spread B={beam} {case}")
+    g = np.random.default_rng(90 + beam)
+    n, d = 1003, 8
+    V = rv(n, d, 91)
+    books = [rv(256, d, 92), rv(100, d, 93, 0.008), rv(256, d, 94, 0.004)]
+    for b in books:
+        b[g.choice(len(b), 5, replace=False)] *= np.float32(300)
+    if case == "long_vectors":
+        V[g.choice(n, 100, replace=False)] *= np.float32(300)
+    if case == "norms_past_fp32":
+        big = g.choice(256, 6, replace=False)
+        books[0][big] = (g.standard_normal((6, d)) * 2e19).astype(np.float32)
+        books[1] = books[1][:7]  # few candidates: all of them fit a wave's list
+        books[1][3] = books[0][big[1]] * np.float32(-0.5)
+        near = g.choice(n, 200, replace=False)
+        V[near] = (books[0][big[g.integers(0, 6, 200)]] * g.uniform(0.5, 1.5, (200, 1))).astype(np.float32)
+        V[near[:50]] *= np.float32(0.1)
+    check_beam(V, books, beam)
+    check_beam(V, books[1:2] + books[2:], beam)
+
+
+def call_us(fn, reps=10):
+    """The least of five timings of reps calls, in microseconds per call."""
+    fn()
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(reps):
+            fn()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / reps)
+    return min(times)
+
+
+@pytest.mark.parametrize("beam", [1, 8])
+def test_beam_small_books_time_of_uneven_inputs(beam):
+    """A long codeword does not widen the other codewords' bounds: long codewords cost no more than ordinary
+    books (measured 1.0 times; 7 to 30 times with one bound for the whole book)."""
+    n, d = 40960, 8
+    V = rv(n, d, 95)
+    plain = [rv(256, d, 96), rv(256, d, 97, 0.008), rv(256, d, 98, 0.004)]
+    spread = [b.copy() for b in plain]
+    for b in spread:
+        b[[3, 77, 200]] *= np.float32(300)
+
+    def us(V, books):
+        vs, bt = VecSet.of_vectors(dev(V)), [dev(b) for b in books]
+        codes = [torch.empty(len(V), dtype=torch.int32, device="cuda") for _ in books]
+        return call_us(lambda: C.crvq_assign_residual_beam(vs, bt, beam, codes))
+
+    p, s = us(V, plain), us(V, spread)
+    say(f"beam B={beam}: ordinary {p:.1f} us, long codewords {s:.1f} us")
+    assert s <= 1.5 * p
