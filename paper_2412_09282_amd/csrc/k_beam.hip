@@ -14,8 +14,10 @@
 // upper bound U of a vector's 32 (64) groups of candidates is no less than its n_next-th smallest distance, so
 // every survivor is among the candidates with lower <= U: about a dozen of 2048, which alone are scored
 // exactly and ranked by their keys.  A vector with more than kCap of them (or a row the screen could not
-// bound, as with a NaN) is searched exactly by its wave.  Bound by VALU issue (about 1040 instructions per 16 rows,
-// 73 % of the cycles).  The width-8 beam over three books of 256 for 286,208 vectors takes 0.72 ms; with
+// bound, as with a NaN) is searched exactly by its wave, in one pass over its candidates: vectors whose distances
+// all tie (later books of zeros) cost about three times the others (4096 of them at width 8 81 us; 398 us with
+// one pass per child).  Bound by VALU issue (about 1040 instructions per 16 rows,
+// 73 % of the cycles).  The width-8 beam over three books of 256 for 286,208 vectors takes 0.66 ms; with
 // per-parent top-8 lists, their re-scored tiles (40 codewords per parent row) and a merge through memory
 // it took 2.27 ms.  Residuals are formed from the vector and the parent's
 // codewords (the same subtractions in the same order), so a step reads and writes codes only.
@@ -163,6 +165,86 @@ __device__ __forceinline__ void vector_list(float (&u)[kBmGroups<PP>], float (&l
   }
   merge_keep<16>(l);
   merge_keep<32>(l);
+}
+
+// The minimum over the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+  v = min(v, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0xB1, 0xf, 0xf, false)));   // lane ^ 1
+  v = min(v, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x4E, 0xf, 0xf, false)));   // lane ^ 2
+  v = min(v, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x141, 0xf, 0xf, false)));  // other four of eight
+  v = min(v, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x140, 0xf, 0xf, false)));  // other eight of 16
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = min(a[0], a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return min(b[0], b[1]);
+}
+
+// The n_next (at most N) smallest keys (distance, parent rank, codeword) of one vector, rank r's in lane r (INT_MAX
+// where no distance up to +inf is left).  Every lane walks its codewords of every parent once, in key order,
+// and keeps the N smallest; the wave then takes the least head of its lists n_next times.
+template <int N>
+__device__ __forceinline__ void exact_children(const double (*xv)[10], const float (*cf)[8], int n_par, int K,
+                                               int n_next, int lane, uint64_t& outD, int& outK) {
+  uint64_t LD[N];
+  int LK[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    LD[j] = kInfBits;
+    LK[j] = INT_MAX;
+  }
+#pragma unroll 1
+  for (int pp = 0; pp < n_par; ++pp) {
+    double x[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = xv[pp][t];
+#pragma unroll N == 1 ? 4 : 1
+    for (int k = lane; k < K; k += 64) {
+      double D = 0.0;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {  // (zeros past d add nothing)
+        const double diff = x[t] - static_cast<double>(cf[k][t]);
+        D = D + diff * diff;
+      }
+      uint64_t b = order_bits(D);
+      int key = (pp << 8) | k;
+      // (an equal distance met later has the larger key; +inf itself still beats an empty slot)
+      if (b < LD[N - 1] || (b == kInfBits && LK[N - 1] == INT_MAX)) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          const bool lt = b < LD[j] || (b == LD[j] && key < LK[j]);
+          const uint64_t tD = lt ? LD[j] : b;
+          const int tk = lt ? LK[j] : key;
+          LD[j] = lt ? b : LD[j];
+          LK[j] = lt ? key : LK[j];
+          b = tD;
+          key = tk;
+        }
+      }
+    }
+  }
+  outD = kInfBits;
+  outK = INT_MAX;
+#pragma unroll 1
+  for (int s = 0; s < n_next; ++s) {
+    const uint32_t hi = static_cast<uint32_t>(LD[0] >> 32), lo = static_cast<uint32_t>(LD[0]);
+    const uint32_t mh = wave_min(hi);
+    const uint32_t ml = wave_min(hi == mh ? lo : 0xffffffffu);
+    const bool top = hi == mh && lo == ml;
+    const uint32_t mk = wave_min(top ? static_cast<uint32_t>(LK[0]) : static_cast<uint32_t>(INT_MAX));
+    if (lane == s) {
+      outD = static_cast<uint64_t>(mh) << 32 | ml;
+      outK = static_cast<int>(mk);
+    }
+    if (top && static_cast<uint32_t>(LK[0]) == mk) {  // keys are distinct: one lane (all of them when none is left)
+#pragma unroll
+      for (int j = 0; j + 1 < N; ++j) {
+        LD[j] = LD[j + 1];
+        LK[j] = LK[j + 1];
+      }
+      LD[N - 1] = kInfBits;
+      LK[N - 1] = INT_MAX;
+    }
+  }
 }
 
 template <int PP, bool PAIRS>
@@ -372,11 +454,9 @@ __global__ __launch_bounds__(64 * kBmWaves, 3) void beam_small_kernel(RowSrc src
     auto exact = [&](int row, int k) {
       double D = 0.0;
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        if (t < d) {
-          const double diff = xr[row][t] - static_cast<double>(cf[k][t]);
-          D = D + diff * diff;
-        }
+      for (int t = 0; t < 8; ++t) {  // (zeros past d add nothing)
+        const double diff = xr[row][t] - static_cast<double>(cf[k][t]);
+        D = D + diff * diff;
       }
       return D;
     };
@@ -398,42 +478,29 @@ __global__ __launch_bounds__(64 * kBmWaves, 3) void beam_small_kernel(RowSrc src
       }
       if (rank < n_next) child(i, v, rank, key >> 8, key & 255, D, false);
     }
-    // the other vectors one by one: n_next times the smallest key past the one before
-    uint64_t todo = __ballot(i < n && !fits);
-    while (todo) {
-      const int vv = ((__ffsll(static_cast<long long>(todo)) - 1) & 15) / PP;
-      todo &= ~((static_cast<uint64_t>((1u << PP) - 1u) << (vv * PP)) * 0x0001000100010001ull);
-      const int64_t iv = ps * V + vv;
-      uint64_t pD = 0;
-      int pk = -1;
-      for (int s = 0; s < n_next; ++s) {
-        uint64_t bD = kInfBits;
-        int bk = INT_MAX;
-        for (int e = lane; e < n_par * K; e += 64) {
-          const int pp = e / K, k = e - pp * K, key = (pp << 8) | k;
-          const uint64_t D = order_bits(exact(vv * PP + pp, k));
-          const bool after = (D > pD) | ((D == pD) & (key > pk));
-          if (after && (D < bD || (D == bD && key < bk))) {
-            bD = D;
-            bk = key;
-          }
+    // the other vectors one by one, all candidates by the whole wave; then their children at once
+    const uint64_t slow = __ballot(i < n && !fits);
+    if (slow) {
+      for (uint64_t todo = slow; todo;) {
+        const int vv = ((__ffsll(static_cast<long long>(todo)) - 1) & 15) / PP;
+        todo &= ~((static_cast<uint64_t>((1u << PP) - 1u) << (vv * PP)) * 0x0001000100010001ull);
+        uint64_t D;
+        int key;
+        if (n_next == 1)
+          exact_children<1>(xr + vv * PP, cf, n_par, K, 1, lane, D, key);
+        else
+          exact_children<8>(xr + vv * PP, cf, n_par, K, n_next, lane, D, key);
+        if (lane < n_next) {
+          candD[vv * 8 + lane] = __builtin_bit_cast(double, D);
+          candK[vv * 8 + lane] = key;
         }
-#pragma unroll
-        for (int m = 1; m < 64; m <<= 1) {
-          const uint64_t oD = __shfl_xor(bD, m);
-          const int ok = __shfl_xor(bk, m);
-          if (oD < bD || (oD == bD && ok < bk)) {
-            bD = oD;
-            bk = ok;
-          }
-        }
-        const bool none = bk == INT_MAX;  // no distance left up to +inf (a NaN row): a defined child
-        if (lane == 0)
-          child(iv, vv, s, none ? 0 : bk >> 8, none ? 0 : bk & 255, __builtin_bit_cast(double, bD), none);
-        if (!none) {
-          pD = bD;
-          pk = bk;
-        }
+      }
+      wave_sync();
+      for (int j = lane; j < V * 8; j += 64) {
+        const int vv = j >> 3, s = j & 7, key = candK[j];
+        if (s >= n_next || ((slow >> (vv * PP)) & 1) == 0) continue;
+        const bool none = key == INT_MAX;  // no distance left up to +inf (a NaN row): a defined child
+        child(ps * V + vv, vv, s, none ? 0 : key >> 8, none ? 0 : key & 255, candD[j], none);
       }
     }
     wave_sync();  // the next pass overwrites the rows and the candidates

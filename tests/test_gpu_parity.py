@@ -629,20 +629,23 @@ def call_us(fn, reps=10):
 
 @pytest.mark.parametrize("beam", [1, 8])
 def test_beam_small_books_time_of_uneven_inputs(beam):
-    """A long codeword does not widen the other codewords' bounds: long codewords cost no more than ordinary
-    books (measured 1.0 times; 7 to 30 times with one bound for the whole book)."""
+    """A long codeword does not widen the other codewords' bounds, and vectors whose distances all tie are not
+    searched once per child: long codewords cost no more than ordinary books (measured 1.0 times; 7 to 30 times
+    with one bound for the whole book), all-zero later books a few times as much (2.4 to 3; 6 to 11)."""
     n, d = 40960, 8
     V = rv(n, d, 95)
     plain = [rv(256, d, 96), rv(256, d, 97, 0.008), rv(256, d, 98, 0.004)]
     spread = [b.copy() for b in plain]
     for b in spread:
         b[[3, 77, 200]] *= np.float32(300)
+    zero = [plain[0], np.zeros((256, d), np.float32), np.zeros((256, d), np.float32)]
 
     def us(V, books):
         vs, bt = VecSet.of_vectors(dev(V)), [dev(b) for b in books]
         codes = [torch.empty(len(V), dtype=torch.int32, device="cuda") for _ in books]
         return call_us(lambda: C.crvq_assign_residual_beam(vs, bt, beam, codes))
 
-    p, s = us(V, plain), us(V, spread)
-    say(f"beam B={beam}: ordinary {p:.1f} us, long codewords {s:.1f} us")
+    p, s, p4, z = us(V, plain), us(V, spread), us(V[:4096], plain), us(V[:4096], zero)
+    say(f"beam B={beam}: ordinary {p:.1f} us, long codewords {s:.1f} us; 4096 vectors {p4:.1f} us, zero books {z:.1f} us")
     assert s <= 1.5 * p
+    assert z <= 4.5 * p4
