@@ -497,22 +497,25 @@ __global__ __launch_bounds__(256) void small_k_final(const double* __restrict__ 
   }
 }
 
-// Few vectors (at most kFewMax): one workgroup per codeword reads all codes, 1024 per wave and step; a wave
-// lists its members in vector order and adds them, eight lanes of dimensions times eight members at a
+// Few vectors (at most kFewMax): one workgroup of 16 waves per codeword reads all codes, 512 per wave and step; a
+// wave lists its members in vector order and adds them, eight lanes of dimensions times eight members at a
 // time, lane group j taking the members j, j + 8, ... of every list; the groups are folded by a fixed
-// butterfly and the waves in order.  One launch and no partials: the latency of reading the codes is
-// what it costs (8192 vectors against 256 codewords 5.8 us; the tables and their fold take 6.5 + 3.0 us,
-// 16384: 9.4 against 6.9 + 3.1, where the line lies).
+// butterfly and the waves in order.  One launch and no partials: the latency of reading the codes is what it
+// costs, and of the members where one code holds most of them (a wave adds 64 in about 2 us, hence 16 waves:
+// four took 115 us for 16384 vectors of one code).  Calls back to back, us, against the tables and their
+// fold: 8192 vectors and 256 codewords 7.1 / 12.9, of one code 18 / 37; 16384: 7.1 / 12.6 and 34 / 39, where the
+// line lies.
 constexpr int64_t kFewMax = 16384;
-constexpr int kFewStep = 1024;
-constexpr int kFewFlush = 64;            // members listed before they are added
+constexpr int kFewWaves = 16;
+constexpr int kFewStep = 512;   // codes per wave and step
+constexpr int kFewFlush = 64;   // members listed before they are added
 constexpr int kFewList = kFewFlush + 64;
 
-__global__ __launch_bounds__(256) void few_vectors_kernel(RowSrc src, const int32_t* __restrict__ codes, void* C, int ct,
-                                                          int32_t* __restrict__ counts) {
-  __shared__ int list_s[4][kFewList];
-  __shared__ double sum_s[4][16];
-  __shared__ int num_s[4];
+__global__ __launch_bounds__(64 * kFewWaves) void few_vectors_kernel(RowSrc src, const int32_t* __restrict__ codes, void* C,
+                                                                      int ct, int32_t* __restrict__ counts) {
+  __shared__ int list_s[kFewWaves][kFewList];
+  __shared__ double sum_s[kFewWaves][16];
+  __shared__ int num_s[kFewWaves];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, k = blockIdx.x;
   int* list = list_s[w];
   const int n = static_cast<int>(src.n), d = src.d, t = lane & 7, grp = lane >> 3;
@@ -521,7 +524,7 @@ __global__ __launch_bounds__(256) void few_vectors_kernel(RowSrc src, const int3
   int held = 0, total = 0;
   auto flush = [&]() {
     wave_lds_sync();
-#pragma unroll 4
+#pragma unroll 8
     for (int j = grp; j < held; j += 8) {
       const int64_t off = row_offset(src, list[j]);
       if (t < d) acc0 = acc0 + row_elem(src, off, t);
@@ -530,15 +533,15 @@ __global__ __launch_bounds__(256) void few_vectors_kernel(RowSrc src, const int3
     wave_lds_sync();
     held = 0;
   };
-  for (int base = w * kFewStep; base < n; base += 4 * kFewStep) {
-    int c[16];
+  for (int base = w * kFewStep; base < n; base += kFewWaves * kFewStep) {
+    int c[kFewStep / 64];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < kFewStep / 64; ++q) {
       const int i = base + 64 * q + lane;
       c[q] = codes[i < n ? i : n - 1];
     }
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < kFewStep / 64; ++q) {
       const bool mine = c[q] == k && base + 64 * q + lane < n;
       const uint64_t m = __ballot(mine);
       if (m) {
@@ -561,10 +564,17 @@ __global__ __launch_bounds__(256) void few_vectors_kernel(RowSrc src, const int3
   }
   if (lane == 0) num_s[w] = total;
   __syncthreads();
-  const int num = num_s[0] + num_s[1] + num_s[2] + num_s[3], e = threadIdx.x;
+  const int e = threadIdx.x;
+  if (e >= 16) return;
+  int num = 0;
+  double sum = 0.0;
+#pragma unroll
+  for (int v = 0; v < kFewWaves; ++v) {
+    num += num_s[v];
+    sum = sum + sum_s[v][e];
+  }
   if (e == 0 && counts) counts[k] = num;
   if (num > 0 && e < d) {
-    const double sum = sum_s[0][e] + sum_s[1][e] + sum_s[2][e] + sum_s[3][e];
     store_centroid(C, ct, k, d, e, sum / static_cast<double>(num));
   }
 }
@@ -948,7 +958,7 @@ hipError_t launch_kmeans_update(const RowSrc& src, const int32_t* codes, int64_t
     const bool aligned = src.d % 8 == 0 && reinterpret_cast<uintptr_t>(src.base) % 16 == 0 && (src.ld * es) % 16 == 0;
     const int kind = aligned ? (src.type == ET_F32 ? 0 : 1) : 2;
     if (n > 0 && n <= kFewMax) {
-      hipLaunchKernelGGL(few_vectors_kernel, dim3(static_cast<unsigned>(K)), dim3(256), 0, stream, src, codes, C, c_type,
+      hipLaunchKernelGGL(few_vectors_kernel, dim3(static_cast<unsigned>(K)), dim3(64 * kFewWaves), 0, stream, src, codes, C, c_type,
                          counts);
       return hipGetLastError();
     }

@@ -649,3 +649,16 @@ def test_beam_small_books_time_of_uneven_inputs(beam):
     say(f"beam B={beam}: ordinary {p:.1f} us, long codewords {s:.1f} us; 4096 vectors {p4:.1f} us, zero books {z:.1f} us")
     assert s <= 1.5 * p
     assert z <= 4.5 * p4
+
+
+@pytest.mark.parametrize("d", [8, 16])
+def test_kmeans_update_few_time_of_one_code(d):
+    """Few vectors that all have one code, so that one workgroup adds them: a few times the call with spread codes
+    (measured 5 times at 16384 vectors of 8, 8 of 16; 14 and 19 times with four waves per codeword)."""
+    n, K = 16384, 256
+    vs, Ct = VecSet.of_vectors(dev(rv(n, d, 99))), dev(rv(K, d, 100))
+    spread = dev(np.random.default_rng(101).integers(0, K, n).astype(np.int32))
+    one = torch.full_like(spread, 7)
+    a, b = call_us(lambda: C.crvq_kmeans_update(vs, spread, Ct)), call_us(lambda: C.crvq_kmeans_update(vs, one, Ct))
+    say(f"kmeans few d={d}: spread codes {a:.1f} us, one code {b:.1f} us")
+    assert b <= 11 * a
