@@ -981,7 +981,11 @@ hipError_t launch_kmeans_update(const RowSrc& src, const int32_t* codes, int64_t
     const int es = src.type == ET_F32 ? 4 : 2;
     const bool aligned = src.d % 8 == 0 && reinterpret_cast<uintptr_t>(src.base) % 16 == 0 && (src.ld * es) % 16 == 0;
     const int kind = aligned ? (src.type == ET_F32 ? 0 : 1) : 2;
-    if (n > 0 && n <= kFewMax) {
+    // (few_vectors_kernel writes the first centroids while vectors are still being read: not where C lies among them)
+    const char *xb = static_cast<const char*>(src.base), *cb = static_cast<const char*>(C);
+    const int64_t x_bytes = ((n - 1) / src.vpr * src.ld + (src.vpr < n ? src.vpr : n) * src.d) * es;
+    const bool apart = cb + K * src.d * (c_type == ET_F32 ? 4 : 2) <= xb || xb + x_bytes <= cb;
+    if (n > 0 && n <= kFewMax && apart) {
       hipLaunchKernelGGL(few_vectors_kernel, dim3(static_cast<unsigned>(K)), dim3(64 * kFewWaves), 0, stream, src, codes, C, c_type,
                          counts);
       return hipGetLastError();

@@ -675,3 +675,23 @@ def test_kmeans_update_time_of_one_bucket():
     a, b = call_us(lambda: C.crvq_kmeans_update(vs, spread, Ct)), call_us(lambda: C.crvq_kmeans_update(vs, one, Ct))
     say(f"kmeans one bucket: spread codes {a:.1f} us, one bucket {b:.1f} us")
     assert b <= 1.7 * a
+
+
+@pytest.mark.parametrize("n,K,pad", [(3000, 256, 0), (16384, 64, 3), (20000, 256, 0)])
+def test_kmeans_update_in_place(n, K, pad):
+    """The codebook as the first K vectors of the vector set itself: all vectors are read before any centroid
+    is written."""
+    say(f"kmeans update in place n={n} K={K} pad={pad}")
+    d = 8
+    g = np.random.default_rng(105)
+    V, q = rv(n, d, 106), g.integers(0, K, n).astype(np.int32)
+    wide = torch.zeros(n, d + pad, device="cuda")
+    wide[:, :d] = dev(V)
+    book = wide.flatten()[: K * d].view(K, d)  # (with padding: K d elements of the first rows)
+    apart = book.clone()
+    vs = VecSet(wide, n, 1, d + pad, d)
+    C.crvq_kmeans_update(VecSet(wide.clone(), n, 1, d + pad, d), dev(q), apart)
+    C.crvq_kmeans_update(vs, dev(q), book)
+    torch.cuda.synchronize()
+    # the sums' order may differ between the two forms: half a last place, and n additions of |v| < 0.2 in fp64
+    np.testing.assert_allclose(book.cpu().numpy(), apart.cpu().numpy(), rtol=2.0 ** -23, atol=1e-15)
