@@ -632,7 +632,11 @@ hipError_t launch_gemv(int64_t M, int64_t N, int64_t n_crit, const uint8_t* q_ba
   const int per_lane = has_ext ? static_cast<int>(cdiv(ext.n * ncv, 64)) : 0;
   const double visits = static_cast<double>(M) * (chunks + per_lane) * (base_type == ET_F32 ? 1.25 : 1.0);
   const size_t rows_lds = gemv_rows_lds(N, base_type == ET_F32 ? 4 : 2, has_ext ? ext.n : 0);
-  if (chunks <= 3 && per_lane <= kRwMaxItems && visits <= 30000.0 && rows_lds <= 160 * 1024) {
+  // y over the memory of x (a square layer's product in place): the tables are formed from all of x before y
+  // is written, the one-pass form's workgroups read x while others write y
+  const char *xb = static_cast<const char*>(x), *yb = reinterpret_cast<const char*>(y);
+  const bool apart = yb + M * 4 <= xb || xb + N * (x_type == ET_F32 ? 4 : 2) <= yb;
+  if (chunks <= 3 && per_lane <= kRwMaxItems && visits <= 30000.0 && rows_lds <= 160 * 1024 && apart) {
     GemvExt used = ext;
     if (!has_ext) used.n = 0;
     const int teams = (kRwThreads / 64) / chunks;

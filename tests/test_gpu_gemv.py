@@ -127,3 +127,17 @@ def test_gemv_rows_bad_entries():
     perm[4000] = N
     got, _ = run_gemv(M, N, 88, books, codes, perm, x, "f32")
     assert np.isnan(got).all()
+
+
+@pytest.mark.parametrize("N,n_ext", [(256, 1), (4096, 0)])
+def test_gemv_in_place(N, n_ext):
+    """A square layer's product written over its own input: all of x is read before y is written."""
+    books, codes, perm, x = make_layer(N, N, 16 * n_ext, n_ext, 256, 256, "f32", 79)
+    exp, a = oracle.gemv(N, N, 8, 16 * n_ext, codes, books, perm, x)
+    q8 = [dev((c & 255).astype(np.uint8)) for c in codes]
+    xy = dev(x)
+    C.crvq_dequant_gemv(N, N, q8[0], N // 8, dev(books[0]), xy, xy, n_crit=16 * n_ext, q_ext=q8[1:], ldq_ext=2,
+                        C_ext=[dev(b) for b in books[1:]], perm=dev(perm))
+    torch.cuda.synchronize()
+    assert (np.abs(xy.cpu().numpy() - exp) <= TOL * a + 1e-30).all()
+    say(f"gemv in place {N}x{N} ext={n_ext}")
