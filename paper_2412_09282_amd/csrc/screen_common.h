@@ -8,6 +8,8 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // at any element
+typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(2)));  // at any bf16 element
 
 __device__ __forceinline__ float bf16_to_f(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
 
@@ -30,41 +32,61 @@ __device__ __forceinline__ double cb_elem(const void* C, int type, int64_t k, in
   return static_cast<double>(bf16_to_f(static_cast<const uint16_t*>(C)[k * d + t]));
 }
 
-// The first DM elements of row i in fp64 (zero past d or for an invalid row).  The type is
-// dispatched once and every load is issued before any is used.
-// DM fp32 / bf16 elements at p as floats: 16-byte vector loads when d fills DM and p is aligned
-// (every lane then reads one contiguous piece), element loads otherwise; zero past d or when !ok.
+// DM fp32 / bf16 elements at p as floats, zero past d or when !ok.  Vector loads, which need no more than element
+// alignment, when d fills DM, and for d = 4 .. 7 of 8: the first and the last four elements, which overlap, in one
+// load each (with element loads the winners' 64 codewords, which the 32 x 32 screen scores exactly, cost more
+// than its products save under 5000 codewords: d = 7, K = 3072 x 1 M rows 464 us, 300 so, 333 on 16 x 16 tiles).
+// Element loads otherwise.
+__device__ __forceinline__ void spread_tail(int d, const f4& b, float& v4, float& v5, float& v6, float& v7) {
+  v4 = d == 5 ? b[3] : d == 6 ? b[2] : d == 7 ? b[1] : 0.0f;
+  v5 = d == 6 ? b[3] : d == 7 ? b[2] : 0.0f;
+  v6 = d == 7 ? b[3] : 0.0f;
+  v7 = 0.0f;
+}
 template <int DM>
 __device__ __forceinline__ void load_f32_elems(const float* p, int d, bool ok, float (&v)[DM]) {
-  if (DM % 4 == 0 && d == DM && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {
+  const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (DM % 4 == 0 && d == DM) {
 #pragma unroll
     for (int q = 0; q < DM / 4; ++q) {
-      const f4 w = ok ? reinterpret_cast<const f4*>(p)[q] : f4{0.0f, 0.0f, 0.0f, 0.0f};
-      v[4 * q] = w[0];
-      v[4 * q + 1] = w[1];
-      v[4 * q + 2] = w[2];
-      v[4 * q + 3] = w[3];
+      const f4 w = ok ? reinterpret_cast<const f4u*>(p)[q] : zero;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[4 * q + t] = w[t];
     }
+  } else if (DM == 8 && d >= 4) {
+    const f4 a = ok ? *reinterpret_cast<const f4u*>(p) : zero, b = ok ? *reinterpret_cast<const f4u*>(p + d - 4) : zero;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] = a[t];
+    spread_tail(d, b, v[4 % DM], v[5 % DM], v[6 % DM], v[7 % DM]);
   } else {
 #pragma unroll
-    for (int t = 0; t < DM; ++t) v[t] = (ok && t < d) ? p[t] : 0.0f;
+    for (int t = 0; t < DM; ++t) v[t] = (DM != 8 || t < 3) && ok && t < d ? p[t] : 0.0f;
   }
 }
 
+__device__ __forceinline__ f4 widen4(const u2u& w) {
+  return f4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u), __uint_as_float(w[1] << 16),
+            __uint_as_float(w[1] & 0xffff0000u)};
+}
 template <int DM>
 __device__ __forceinline__ void load_bf16_elems(const uint16_t* p, int d, bool ok, float (&v)[DM]) {
-  if (DM % 4 == 0 && d == DM && (reinterpret_cast<uintptr_t>(p) & 7) == 0) {
+  const u2u zero = {0u, 0u};
+  if (DM % 4 == 0 && d == DM) {
 #pragma unroll
     for (int q = 0; q < DM / 4; ++q) {
-      const uint2 w = ok ? reinterpret_cast<const uint2*>(p)[q] : make_uint2(0u, 0u);
-      v[4 * q] = __uint_as_float(w.x << 16);
-      v[4 * q + 1] = __uint_as_float(w.x & 0xffff0000u);
-      v[4 * q + 2] = __uint_as_float(w.y << 16);
-      v[4 * q + 3] = __uint_as_float(w.y & 0xffff0000u);
+      const f4 w = widen4(ok ? reinterpret_cast<const u2u*>(p)[q] : zero);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[4 * q + t] = w[t];
     }
+  } else if (DM == 8 && d >= 4) {
+    const u2u a = ok ? *reinterpret_cast<const u2u*>(p) : zero, b = ok ? *reinterpret_cast<const u2u*>(p + d - 4) : zero;
+    const f4 w = widen4(a);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] = w[t];
+    spread_tail(d, widen4(b), v[4 % DM], v[5 % DM], v[6 % DM], v[7 % DM]);
   } else {
 #pragma unroll
-    for (int t = 0; t < DM; ++t) v[t] = (ok && t < d) ? bf16_to_f(p[t]) : 0.0f;
+    for (int t = 0; t < DM; ++t) v[t] = (DM != 8 || t < 3) && ok && t < d ? bf16_to_f(p[t]) : 0.0f;
   }
 }
 
