@@ -356,16 +356,32 @@ crvq_status crvq_assign_residual_beam(const void* X, int x_dtype, int64_t n_rows
     outs.q[t] = codes[t];
     outs.ld[t] = ldc ? ldc[t] : vecs_per_row;
   }
+  // The one-launch form's last step writes codes and errors while vectors and books are still being read; outputs
+  // in their memory are written by the general form's last launch instead.
+  const size_t x_span = static_cast<size_t>((n_rows - 1) * ld + vecs_per_row * d) * esize(x_dtype);
+  bool apart = !(err && overlaps(err, static_cast<size_t>(n) * 4, X, x_span));
+  for (int t = 0; t < n_books; ++t) {
+    const size_t span = static_cast<size_t>((n_rows - 1) * outs.ld[t] + vecs_per_row) * 4;
+    apart = apart && !overlaps(codes[t], span, X, x_span);
+    for (int b = 0; b < n_books; ++b) {
+      const size_t b_span = static_cast<size_t>(Ks[b] * d) * esize(book_dtypes[b]);
+      apart = apart && !overlaps(codes[t], span, books[b], b_span) &&
+              !(err && overlaps(err, static_cast<size_t>(n) * 4, books[b], b_span));
+    }
+  }
+  auto small_form = [&](int t, int64_t parents) {
+    return beam_small_form(d, Ks[t], parents, beam) && (apart || t + 1 < n_books);
+  };
   int64_t n_par = 1;
   int cur = 0;
   for (int t = 0; t < n_books; ++t) {
     const int64_t nn = n_par * Ks[t], n_next = nn < beam ? nn : beam;
     hipError_t e;
-    if (beam_small_form(d, Ks[t], n_par, beam)) {
+    if (small_form(t, n_par)) {
       // one launch; the residuals only where the next step needs them, and of the last step's children
       // only the first
       const bool last = t + 1 == n_books;
-      const bool res = !last && !beam_small_form(d, Ks[t + 1], n_next, beam);
+      const bool res = !last && !small_form(t + 1, n_next);
       e = launch_beam_small(src0, static_cast<int>(n_par), last ? 1 : static_cast<int>(n_next), t, n_books, books,
                             book_dtypes, Ks[t], w.tup[cur], w.tup[cur ^ 1], res ? w.res[cur ^ 1] : nullptr, last, outs,
                             vecs_per_row, err, st);

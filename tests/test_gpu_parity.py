@@ -695,3 +695,28 @@ def test_kmeans_update_in_place(n, K, pad):
     torch.cuda.synchronize()
     # the sums' order may differ between the two forms: half a last place, and n additions of |v| < 0.2 in fp64
     np.testing.assert_allclose(book.cpu().numpy(), apart.cpu().numpy(), rtol=2.0 ** -23, atol=1e-15)
+
+
+@pytest.mark.parametrize("beam", [1, 4])
+@pytest.mark.parametrize("over", ["vectors", "book"])
+def test_beam_small_books_outputs_in_place(beam, over):
+    """Codes and errors in the memory of the vectors, or codes in that of a book: everything is read before they
+    are written."""
+    say(f"beam outputs over {over} B={beam}")
+    n, d = 5000, 8
+    V = rv(n, d, 107)
+    books = [rv(256, d, 108), rv(256, d, 109, 0.005)]
+    exp_codes, exp_err = oracle.beam(V, books, beam)
+    X, bt = dev(V), [dev(b) for b in books]
+    if over == "vectors":
+        words = X.view(torch.int32).flatten()
+        codes, err = [words[:n], words[n : 2 * n]], X.flatten()[2 * n : 3 * n]
+    else:
+        X, n = X[:900], 900
+        exp_codes, exp_err = exp_codes[:, :n], exp_err[:n]
+        codes, err = [bt[0].view(torch.int32).flatten()[:n], bt[1].view(torch.int32).flatten()[:n]], None
+    C.crvq_assign_residual_beam(VecSet(X, n, 1, d, d), bt, beam, codes, err)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(np.stack([c.cpu().numpy() for c in codes]), exp_codes)
+    if err is not None:
+        np.testing.assert_array_equal(err.cpu().numpy(), exp_err.astype(np.float32))
