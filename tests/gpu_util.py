@@ -1,11 +1,13 @@
 """Helpers shared by the GPU parity tests (comparison rules; no method arithmetic beyond the
 oracle's own definitions)."""
+import ctypes
 import sys
 
 import numpy as np
 import torch
 
 import oracle
+from paper_2412_09282_amd import crvq
 
 TIE_REL = 1e-6  # codes may differ only where the distance gap is below this (relative)
 
@@ -68,3 +70,16 @@ def rel_close(got: np.ndarray, exp: np.ndarray, tol: float, what: str, axis_vec:
         den = np.abs(exp)
     ok = num <= tol * den + 1e-30
     assert ok.all(), f"{what}: {int((~ok).sum())} entries beyond rel {tol}; worst {float((num / (den + 1e-300)).max())}"
+
+
+class SearchPlan(ctypes.Structure):
+    """crvq::ScreenPlan (crvq_internal.h): the form a nearest-codeword search takes at a shape."""
+    _fields_ = [(f, ctypes.c_int) for f in ("nb", "cb", "ks", "split", "chunk", "s32", "prune")] + \
+        [("tiles", ctypes.c_int64), ("grid_x", ctypes.c_int64), ("splits", ctypes.c_int), ("tiles_per_split", ctypes.c_int64)]
+
+
+def search_plan(n: int, d: int, K: int, top: int = 1) -> SearchPlan:
+    """The library's own plan (host code), so that a test can state the form it means to reach."""
+    f = crvq.lib()._ZN4crvq11plan_screenElili  # ScreenPlan crvq::plan_screen(int64_t, int, int64_t, int)
+    f.argtypes, f.restype = [ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_int], SearchPlan
+    return f(n, d, K, top)

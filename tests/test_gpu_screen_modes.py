@@ -15,7 +15,7 @@ from paper_2412_09282_amd import crvq as C
 from paper_2412_09282_amd import inputs
 from paper_2412_09282_amd.crvq import VecSet
 
-from gpu_util import dev, say
+from gpu_util import dev, say, search_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -41,6 +41,29 @@ def check(V, Cb, dtype="f32"):
     bad = np.flatnonzero(got != exp)
     assert len(bad) == 0, f"{len(bad)} codes differ, e.g. rows {bad[:5]} got {got[bad[:5]]} want {exp[bad[:5]]}"
     np.testing.assert_array_equal(gd, ed.astype(np.float32))
+
+
+def check_pruned(V, Cb, dtype="f32"):
+    """A call whose plan prunes: the codes and distances of every row against those of the same rows in pieces whose
+    plan does not, and of a sample of the rows against the oracle."""
+    n, d = V.shape
+    K, piece = Cb.shape[0], 131072
+    assert search_plan(n, d, K).prune == 1, f"n={n} K={K} does not prune"
+    assert search_plan(piece, d, K).prune == 0
+    Vt, Ct = dev(V, dtype), dev(Cb, dtype)
+    codes, ref = (torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    dist, refd = (torch.empty(n, dtype=torch.float32, device="cuda") for _ in range(2))
+    C.crvq_assign(VecSet.of_vectors(Vt), Ct, codes, dist)
+    for a in range(0, n, piece):
+        b = min(n, a + piece)
+        C.crvq_assign(VecSet.of_vectors(Vt[a:b]), Ct, ref[a:b], refd[a:b])
+    torch.cuda.synchronize()
+    assert torch.equal(codes, ref), f"{int((codes != ref).sum())} codes differ from the unpruned search"
+    assert torch.equal(dist, refd)
+    S = np.random.default_rng(1).choice(n, 40000, replace=False)
+    exp, ed = oracle.assign(V[S], Cb, dtype, dtype)
+    np.testing.assert_array_equal(codes.cpu().numpy()[S], exp)
+    np.testing.assert_array_equal(dist.cpu().numpy()[S], ed.astype(np.float32))
 
 
 @pytest.mark.parametrize("n,K,d", [(65536, 65536, 8), (65536 + 37, 65536 - 5, 8), (70001, 32768 + 17, 5)])
@@ -135,6 +158,7 @@ def test_beam_width_one_long_extended_book(n):
     order at 1,048,613), whose operands are the residuals rounded to fp32; the certificate adds that
     rounding to each row's own fp16 remainder."""
     say(f"residual beam, width 1, K=4096 basic + K=65536 extended over fp64 residuals, n={n}")
+    assert search_plan(n, 8, 65536).prune == (1 if n > 1000000 else 0)
     V = rv(n, 8, 81)
     books = [rv(4096, 8, 82), rv(65536, 8, 83, 0.006)]
     codes = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in books]
@@ -186,10 +210,14 @@ def test_two_pass_screen(case):
 # two fp16 values after the power-of-two scale (each y2_t positive and 2^-13 short of half a spacing,
 # the largest it can be), and the codewords share the rows' signs, so sum_t a_t y2_t is close to its
 # Cauchy-Schwarz bound; the codewords come in near-tied pairs, so many rows stay uncertain.  Codes
-# and distances must remain the oracle's (unpruned: 4 codebook splits; pruned: one split, key order).
-@pytest.mark.parametrize("n,K", [(262144 + 37, 65536), ((1 << 20) + 37, 16384)])
-def test_first_screen_aligned_remainders(n, K):
+# and distances must remain the oracle's (unpruned in one and in four codebook splits; pruned: one split, key
+# order).
+@pytest.mark.parametrize("n,K,splits,prune", [(262144 + 37, 65536, 4, 0), ((1 << 20) + 37, 16384, 1, 0),
+                                              (400037, 65536, 1, 1), (1600037, 16384, 1, 1)])
+def test_first_screen_aligned_remainders(n, K, splits, prune):
     d = 8
+    p = search_plan(n, d, K)
+    assert (p.s32, p.splits, p.prune) == (1, splits, prune)
     say(f"first screen, remainders aligned with the codewords: n={n} K={K}")
     g = np.random.default_rng(71)
     # -2^12 x in [256, 512), where fp16 values are 0.25 apart: 256 + 0.25 j + (0.125 - 2^-13), exact in fp32
@@ -200,20 +228,21 @@ def test_first_screen_aligned_remainders(n, K):
     e2 = (g.random((K // 2, d)) * 2e-6).astype(np.float32)
     Cb = np.ascontiguousarray(np.concatenate([base - e1, base - e2])[g.permutation(K)])
     assert (Cb < 0).all() and (V < 0).all()
-    check(V, Cb)
+    (check_pruned if prune else check)(V, Cb)
 
 
-def test_second_screen_own_rows_full():
+@pytest.mark.parametrize("K", [4096, 16384])
+def test_second_screen_own_rows_full(K):
     """From 2^23 rows up the second (split) screen of fp32 rows gives every wave rows of its own
-    instead of sharing them across a workgroup.  Every row of a (2^23 + 37)-row search against 4096
-    codewords drawn next to the rows (so several percent of the rows reach the second screen) is
-    compared with the oracle."""
-    n, K, d = (1 << 23) + 37, 4096, 8
+    instead of sharing them across a workgroup.  Every row of a (2^23 + 37)-row search against codewords drawn
+    next to the rows (so several percent of the rows reach the second screen) is compared with the oracle (4096
+    codewords, unpruned) or with the unpruned search (16384, pruned)."""
+    n, d = (1 << 23) + 37, 8
     say(f"two-pass screen fp32 n={n} K={K}: second screen with rows per wave, full comparison")
     g = np.random.default_rng(51)
     V = rv(n, d, 52)
     Cb = np.ascontiguousarray(V[g.choice(n, K, replace=False)] + rv(K, d, 53, 0.002))
-    check(V, Cb)
+    (check if K == 4096 else check_pruned)(V, Cb)
 
 
 # From 2.5e10 pairs and 16384 codewords up the first screen visits the codebook in the order
@@ -223,18 +252,19 @@ def test_second_screen_own_rows_full():
 # (no spread to bin); "outlier_cols": heavy tails with 10x outlier coordinates in 8 % of the vectors
 # (the bins follow the bulk, the outliers fall into the end bins); "d1": one dimension (both key
 # coordinates are the same one).
-@pytest.mark.parametrize("case,K", [("near", 65536), ("bf16", 16384), ("outliers", 16384), ("ties", 16384),
-                                    ("tiny", 4096), ("constant", 16384), ("outlier_cols", 16384),
-                                    ("d1", 4096)])
-def test_pruned_first_screen(case, K):
-    n, d = (1 << 20) + 4096 + 37, (1 if case == "d1" else 8)
+@pytest.mark.parametrize("case,n,K", [("near", (1 << 20) + 4133, 65536), ("bf16", 1600037, 16384),
+                                      ("outliers", 1600037, 16384), ("ties", 400037, 65536), ("tiny", 400037, 65536),
+                                      ("constant", 400037, 65536), ("outlier_cols", 1600037, 16384),
+                                      ("d1", 400037, 65536)])
+def test_pruned_first_screen(case, n, K):
+    d = 1 if case == "d1" else 8
     say(f"pruned first screen n={n} K={K} ({case})")
     g = np.random.default_rng(60)
     if case in ("near", "bf16"):
         V = rv(n, d, 61)
         Cb = np.ascontiguousarray(V[g.choice(n, K, replace=False)] + rv(K, d, 62, 0.002))
         if case == "bf16":
-            check(inputs.f32_to_bf16_bits(V), inputs.f32_to_bf16_bits(Cb), "bf16")
+            check_pruned(inputs.f32_to_bf16_bits(V), inputs.f32_to_bf16_bits(Cb), "bf16")
             return
     elif case == "outliers":
         Cb = (g.standard_t(4.0, size=(K, d)) * 0.02).astype(np.float32)
@@ -265,7 +295,7 @@ def test_pruned_first_screen(case, K):
     else:  # magnitudes far below one: the bands are kept in units of the codebook scale
         V = rv(n, d, 65) * np.float32(1e-30)
         Cb = rv(K, d, 66) * np.float32(1e-30)
-    check(V, Cb)
+    check_pruned(V, Cb)
 
 
 def hard_inputs(case, n, K, d, g):
@@ -293,6 +323,7 @@ def hard_inputs(case, n, K, d, g):
 def test_pruned_long_books(case, n, K, d):
     """The pruned screen just above the pairs it starts at."""
     say(f"pruned screen n={n} K={K} d={d} ({case})")
+    assert search_plan(n, d, K).prune == 1
     V, Cb = hard_inputs(case, n, K, d, np.random.default_rng(80))
     if case == "bf16":
         check(inputs.f32_to_bf16_bits(V), inputs.f32_to_bf16_bits(Cb), "bf16")
@@ -308,6 +339,8 @@ def test_pruned_long_books(case, n, K, d):
 def test_split_form_at_once(case, n, K, d):
     """Middle lengths: 32 x 32 tiles in the split form for every row, around the lines of the dispatch."""
     say(f"split form at once n={n} K={K} d={d} ({case})")
+    p = search_plan(n, d, K)
+    assert (p.s32, p.prune) == (0 if (n, K) in ((243001, 2048), (600011, 2047)) else 1, 0)
     V, Cb = hard_inputs(case, n, K, d, np.random.default_rng(85))
     if case == "bf16":
         check(inputs.f32_to_bf16_bits(V), inputs.f32_to_bf16_bits(Cb), "bf16")
@@ -338,6 +371,7 @@ def test_rescue_of_most_rows():
     base = rv(16384, 8, 45)
     Cb = np.ascontiguousarray(np.concatenate([base, base, base, base])[g.permutation(65536)])
     n = 1048579
+    assert search_plan(n, 8, 65536).prune == 1
     V = np.ascontiguousarray(base[g.integers(0, 16384, n)])
     codes = torch.empty(n, dtype=torch.int32, device="cuda")
     dist = torch.empty(n, dtype=torch.float32, device="cuda")
