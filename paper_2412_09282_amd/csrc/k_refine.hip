@@ -480,6 +480,7 @@ __device__ __forceinline__ int wave_min_i32(int v) {
   return min(static_cast<int>(b[0]), static_cast<int>(b[1]));
 }
 constexpr int kNoKey = 0x7fffffff;
+constexpr int kMany = 9;  // equal rounded scores from which a wave reduces the exact ones instead of walking them
 // f rounded to fp32, as an integer of the same order; kNoKey when that is +inf or NaN.
 __device__ __forceinline__ int order_key(double f) {
   const float x = static_cast<float>(f);
@@ -614,15 +615,33 @@ __global__ __launch_bounds__(64 * kRwWaves) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
         for (int j = 0; j < 4; ++j) m[j] = __ballot(key[i][j] == bi);
         int bk = cur[i];
-        if (bi != kNoKey && __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]) == 1) {
+        const int least = bi == kNoKey ? kMany : __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]);
+        if (least == 1) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) bk = m[j] ? 64 * j + __ffsll(static_cast<long long>(m[j])) - 1 : bk;
+        } else if (least >= kMany) {
+          // many (a book of equal codewords), or f beyond fp32: every lane's own least, then the wave's, the
+          // lowest codeword of equal ones; +inf and NaN never win
+          double v = __builtin_inf();
+          int k = kNoKey;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const bool better = (bi == kNoKey || key[i][j] == bi) && f[i][j] < v;
+            v = better ? f[i][j] : v;
+            k = better ? 64 * j + lane : k;
+          }
+          int64_t o = __builtin_bit_cast(int64_t, v + 0.0);  // (no -0)
+          o ^= (o >> 63) & 0x7fffffffffffffffll;
+          const int hi = static_cast<int>(o >> 32), lo = static_cast<int>(static_cast<uint32_t>(o) ^ 0x80000000u);
+          const int mh = wave_min_i32(hi), ml = wave_min_i32(hi == mh ? lo : kNoKey);
+          const int mk = wave_min_i32(hi == mh && lo == ml ? k : kNoKey);
+          bk = mk == kNoKey ? bk : mk;
         } else {
-          // several (or f beyond fp32): the exact values in ascending codeword order; +inf and NaN never win
+          // a few: the exact values in ascending codeword order
           double fb = __builtin_inf();
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            uint64_t mj = bi == kNoKey ? __ballot(f[i][j] < __builtin_inf()) : m[j];
+            uint64_t mj = m[j];
             while (mj) {
               const int l = __ffsll(static_cast<long long>(mj)) - 1;
               mj &= mj - 1;
