@@ -16,8 +16,8 @@
 // exactly and ranked by their keys.  A vector with more than kCap of them (or a row the screen could not
 // bound, as with a NaN) is searched exactly by its wave, in one pass over its candidates: vectors whose distances
 // all tie (later books of zeros) cost about three times the others (4096 of them at width 8 81 us; 398 us with
-// one pass per child).  Bound by VALU issue (about 1040 instructions per 16 rows,
-// 73 % of the cycles).  The width-8 beam over three books of 256 for 286,208 vectors takes 0.66 ms; with
+// one pass per child).  Bound by VALU issue (about 1010 instructions per 16 rows,
+// 74 % of the cycles).  The width-8 beam over three books of 256 for 286,208 vectors takes 0.66 ms; with
 // per-parent top-8 lists, their re-scored tiles (40 codewords per parent row) and a merge through memory
 // it took 2.27 ms.  Residuals are formed from the vector and the parent's
 // codewords (the same subtractions in the same order), so a step reads and writes codes only.

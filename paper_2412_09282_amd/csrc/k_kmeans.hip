@@ -332,8 +332,9 @@ __device__ __forceinline__ void add_vector(const RowSrc& s, int64_t off, double 
 }
 
 // ---- small codebooks (K <= 256): per-wave tables, no sort ----------------------------------------
-// Dimensions in halves of 8 (blockIdx.y; two at d > 8, where 1 M vectors of 16 take 34 us against 198 us
-// for one thread per code over LDS-sorted rounds).  Every wave owns a private fp64 table of K x 8 sums in LDS and the batches of 64 vectors
+// Dimensions in halves of 8 (blockIdx.y; two at d > 8, where 1 M vectors of 16 take 50 us with the fold of the
+// partials against 141 us for one thread per code over LDS-sorted rounds).
+// Every wave owns a private fp64 table of K x 8 sums in LDS and the batches of 64 vectors
 // j = wave, wave + W, wave + 2W, ... (W waves in the grid), so the waves in flight read one moving
 // window of memory.  It reads one vector per lane, kSkDepth batches in flight; within a batch the
 // lanes that share a code find each other with eight ballots, and the lowest of them adds its peers'

@@ -68,8 +68,9 @@ __device__ __forceinline__ void merge_groups(float& m1, float& m2) {
 // cell can reach its distance (the bound of finalize_kernel with R = ||x|| + sqrt(D)).  The other rows
 // (about one in 300) are searched exactly by their wave.  fp64 distances are formed only where they are
 // asked for.  FT: packed aligned rows of one type (packed_row), 0 any layout; H: halves of 8
-// dimensions.  Bound by VALU issue (about 1700 instructions per 128 rows of 8, a third of them the split
-// of the rows).  5.6 M fp32 rows of 8 against 256 codewords: 188 us; with a codebook launch, every winning
+// dimensions.  Bound by VALU issue (about 1800 instructions per 128 rows of 8, a third of them the split
+// of the rows; 80 % of the cycles).  5.6 M fp32 rows of 8 against 256 codewords: 185 us;
+// with a codebook launch, every winning
 // cell scored in fp64, six operations per cell and a rescue launch 250 us.  1 M rows of 16: 65 us (fp32
 // matrix instructions and a finalize pass 186 us).  8192 rows: 5 us (17 us in three launches).
 template <int H, int FT, int CB>
