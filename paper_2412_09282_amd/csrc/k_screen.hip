@@ -1266,24 +1266,71 @@ __device__ __forceinline__ float min_fold16(float c, const f16v& a) {
 __device__ __forceinline__ uint16_t f16_bits(float v) { return __builtin_bit_cast(uint16_t, static_cast<_Float16>(v)); }
 __device__ __forceinline__ float f16_val(uint16_t b) { return static_cast<float>(__builtin_bit_cast(_Float16, b)); }
 
-// Partial maxima of |c| over the codebook (block b covers a strided share).
-__global__ __launch_bounds__(256) void cb_absmax_partial(const void* __restrict__ C, int ct, int64_t count,
-                                                         float* __restrict__ part) {
-  __shared__ float sh[256];
-  float m = 0.0f;
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; e < count;
-       e += static_cast<int64_t>(gridDim.x) * 256) {
-    const float v = (ct == ET_F32) ? static_cast<const float*>(C)[e]
-                                   : bf16_to_f(static_cast<const uint16_t*>(C)[e]);
-    m = fmaxf(m, fabsf(v));
+// Codewords that occur more than once leave every row next to them uncertain where their copies lie in different
+// chunks: the rest equals the best.  Only the first copy can be an answer (ties go to the lowest index), so the
+// others are packed as padding.  They are found through a table of slots by a hash of the value, which holds
+// the lowest codeword of each slot.  The table is not cleared: an entry counts only if it is a codeword that belongs
+// to its slot, and one that does may stand there before it was entered (entries are ~k, which the distances that
+// stood there before hardly ever are).  Two different codewords of one slot hide each other's copies, which then
+// cost what they did.  Half of the codewords copies, 2048 x 262,144 rows: 1063 us -> 92; 65536 x 1 M 26.9 ms
+// -> 2.1; books without copies as before to 1 % (both kernels fold their maxima without a tree of barriers, which
+// pays for the table).
+__device__ __forceinline__ uint32_t cb_slot(const float (&v)[8], uint32_t mask) {
+  uint32_t h = 0;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const uint32_t b = v[t] == 0.0f ? 0u : __float_as_uint(v[t]);  // the zeros are equal
+    h = (h ^ b) * 0x9e3779b1u;
+    h ^= h >> 15;
   }
-  sh[threadIdx.x] = m;
+  return h & mask;
+}
+
+__device__ __forceinline__ void cb_values(const void* C, int ct, int64_t k, int d, float (&v)[8]) {
+  if (ct == ET_F32)
+    load_f32_elems<8>(static_cast<const float*>(C) + k * d, d, true, v);
+  else
+    load_bf16_elems<8>(static_cast<const uint16_t*>(C) + k * d, d, true, v);
+}
+
+// The largest m of a block of 256 (every thread gets it).
+__device__ __forceinline__ float block_max256(float m, float (&sh)[4]) {
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1) m = fmaxf(m, __shfl_xor(m, s));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
   __syncthreads();
-  for (int s = 128; s >= 1; s >>= 1) {
-    if (static_cast<int>(threadIdx.x) < s) sh[threadIdx.x] = fmaxf(sh[threadIdx.x], sh[threadIdx.x + s]);
-    __syncthreads();
+  return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+}
+
+// Partial maxima of |c| over the codebook (block b covers a strided share), and the table.
+__global__ __launch_bounds__(256) void cb_absmax_partial(const void* __restrict__ C, int ct, int64_t K, int d,
+                                                         float* __restrict__ part, int* __restrict__ table,
+                                                         uint32_t mask) {
+  __shared__ float sh[4];
+  float m = 0.0f;
+  for (int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; k < K;
+       k += static_cast<int64_t>(gridDim.x) * 256) {
+    float v[8];
+    cb_values(C, ct, k, d, v);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) m = fmaxf(m, fabsf(v[t]));
+    const uint32_t slot = cb_slot(v, mask);
+    int old = __hip_atomic_load(table + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // Every failed exchange means that another codeword of the slot was entered, and those only get lower
+    for (;;) {
+      const int has = ~old;
+      if (has >= 0 && has <= k) {
+        float o[8];
+        cb_values(C, ct, has, d, o);
+        if (cb_slot(o, mask) == slot) break;
+      }
+      const int seen = atomicCAS(table + slot, old, ~static_cast<int>(k));
+      if (seen == old) break;
+      old = seen;
+    }
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+  m = block_max256(m, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = m;
 }
 
 // alpha = 2^(11 - floor(log2 max)), at most 2^126; 1 for an all-zero or non-finite codebook.
@@ -1300,29 +1347,36 @@ __global__ __launch_bounds__(256) void prep_codebook_s32(const void* __restrict_
                                                          int64_t tiles, const float* __restrict__ part, int nparts,
                                                          const int* __restrict__ corder,
                                                          uint16_t* __restrict__ apack, float* __restrict__ alpha_out,
-                                                         int* __restrict__ rcount) {
-  __shared__ float sh[256];
-  sh[threadIdx.x] = (static_cast<int>(threadIdx.x) < nparts) ? part[threadIdx.x] : 0.0f;
-  __syncthreads();
-  for (int s = 128; s >= 1; s >>= 1) {
-    if (static_cast<int>(threadIdx.x) < s) sh[threadIdx.x] = fmaxf(sh[threadIdx.x], sh[threadIdx.x + s]);
-    __syncthreads();
+                                                         int* __restrict__ rcount, const int* __restrict__ table,
+                                                         uint32_t mask) {
+  __shared__ float sh[4];
+  const int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  const float mx = static_cast<int>(threadIdx.x) < nparts ? part[threadIdx.x] : 0.0f;
+  // position k holds codeword corder[k] when the book is packed in key order
+  int64_t ks = (k < K) ? (corder ? static_cast<int64_t>(corder[k]) : k) : -1;
+  if (ks >= K) ks = -1;
+  float c[8] = {};
+  if (ks >= 0) cb_values(C, ct, ks, d, c);
+  if (ks >= 0) {
+    const int first = ~table[cb_slot(c, mask)];
+    if (first >= 0 && first < ks) {
+      float o[8];
+      cb_values(C, ct, first, d, o);
+      bool same = true;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) same = same && o[t] == c[t];
+      if (same) ks = -1;
+    }
   }
-  const float alpha = s32_alpha(sh[0]);
+  const float alpha = s32_alpha(block_max256(mx, sh));
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     alpha_out[0] = alpha;
     rcount[0] = 0;  // rows left uncertain by the first screen
     rcount[1] = 0;  // rows left uncertain by the second (split) screen of those
   }
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (k >= tiles * kS32Tile) return;
-  // position k holds codeword corder[k] when the book is packed in key order
-  int64_t ks = (k < K) ? (corder ? static_cast<int64_t>(corder[k]) : k) : -1;
-  if (ks >= K) ks = -1;
-  float c[8];
 #pragma unroll
-  for (int t = 0; t < 8; ++t)
-    c[t] = (ks >= 0 && t < d) ? alpha * static_cast<float>(cb_elem(C, ct, ks, d, t)) : 0.0f;
+  for (int t = 0; t < 8; ++t) c[t] = ks >= 0 ? alpha * c[t] : 0.0f;
   u16x8 p1, p2, pn;
   float N = 0.0f;
 #pragma unroll
@@ -3004,13 +3058,16 @@ hipError_t launch_screen(const RowSrc& src, const void* C, int ct, int64_t K, in
   if (top == 1 && K <= 256) return launch_assign_small(src, C, ct, K, out_codes, out_dist, rowD, rowK, stream);
   hipError_t e;
   if (p.s32) {
-    const int64_t count = K * src.d;
-    int nparts = static_cast<int>(cdiv(count, 4096));
-    if (nparts > kS32MaxParts) nparts = kS32MaxParts;
-    if (nparts < 1) nparts = 1;
+    const int nparts = static_cast<int>(cdiv(K, 256) < kS32MaxParts ? cdiv(K, 256) : kS32MaxParts);
+    // the table, in the memory of the distances that the screen writes later: 32 to 64 slots per codeword where
+    // they fit
+    int* const table = reinterpret_cast<int*>(w.pD);
+    uint32_t mask = 1;
+    while (mask < 32 * K && 2 * static_cast<int64_t>(mask + 1) <= 2 * p.splits * src.n) mask = 2 * mask + 1;
     float* alpha = w.smax + kS32MaxParts;
     uint16_t* ap = reinterpret_cast<uint16_t*>(w.apack);
-    hipLaunchKernelGGL(cb_absmax_partial, dim3(nparts), dim3(256), 0, stream, C, ct, count, w.smax);
+    hipLaunchKernelGGL(cb_absmax_partial, dim3(nparts), dim3(256), 0, stream, C, ct, K, src.d, w.smax,
+                       table, mask);
     PruneData pd = {};
     const int jp = 0;                    // the coordinate of the second band
     const int jq = src.d > 1 ? 1 : 0;    // and of the third
@@ -3043,7 +3100,7 @@ hipError_t launch_screen(const RowSrc& src, const void* C, int ct, int64_t K, in
                          dim3(static_cast<unsigned>(cdiv(K, kPruneCbTile))), dim3(kPruneCbThreads), 0, stream,
                          w.ckey, K, w.hist, w.corder);
       hipLaunchKernelGGL(prep_codebook_s32, dim3(static_cast<unsigned>(cdiv(p.tiles * kS32Tile, 256))), dim3(256), 0,
-                         stream, C, ct, K, src.d, p.tiles, w.smax, nparts, w.corder, ap, alpha, w.rcount);
+                         stream, C, ct, K, src.d, p.tiles, w.smax, nparts, w.corder, ap, alpha, w.rcount, table, mask);
       hipLaunchKernelGGL(prune_chunks_kernel, dim3(static_cast<unsigned>(cdiv(nch, 4))), dim3(256), 0, stream, C, ct,
                          K, src.d, jp, jq, w.corder, alpha, nch, w.cbnd, w.cbnd3);
       hipLaunchKernelGGL(prune_envelope_kernel, dim3(1), dim3(1024), 0, stream, w.cbnd, static_cast<int>(nch), w.cminS,
@@ -3068,7 +3125,7 @@ hipError_t launch_screen(const RowSrc& src, const void* C, int ct, int64_t K, in
       pd.jq = jq;
     } else {
       hipLaunchKernelGGL(prep_codebook_s32, dim3(static_cast<unsigned>(cdiv(p.tiles * kS32Tile, 256))), dim3(256), 0,
-                         stream, C, ct, K, src.d, p.tiles, w.smax, nparts, nullptr, ap, alpha, w.rcount);
+                         stream, C, ct, K, src.d, p.tiles, w.smax, nparts, nullptr, ap, alpha, w.rcount, table, mask);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     dim3 grid(static_cast<unsigned>(p.grid_x), static_cast<unsigned>(p.splits));
